@@ -116,6 +116,22 @@ size_t gate_workspace_bytes(const moe_gate_params* p) {
   return ((h + 255) & ~static_cast<size_t>(255)) + static_cast<size_t>(p->S) * static_cast<size_t>(p->E) * 4;
 }
 
+// What the gate asks for: with a projection whose K is worth splitting over
+// blocks, also room for the ranges' partial logits, fp32 [z, S, E], in place of
+// the one logits buffer.  A workspace without that room is served too: one
+// block then takes all ranges of its tokens.
+TileSplit gate_split(const moe_gate_params* p) {
+  if (p->kind == MOE_GATE_HASH || p->logits_in) return {1, 1};
+  return route_tile_split(p->S, p->d, p->E, p->dtype);
+}
+
+size_t gate_split_bytes(const moe_gate_params* p) {
+  const TileSplit t = gate_split(p);
+  if (t.z < 2) return 0;
+  return ((gate_hist_bytes(p) + 255) & ~static_cast<size_t>(255)) +
+         static_cast<size_t>(t.z) * static_cast<size_t>(p->S) * static_cast<size_t>(p->E) * 4;
+}
+
 moe_status check_layout(const moe_layout* l, const char* who) {
   if (!l) return fail(MOE_ERR_INVALID_ARG, "%s: layout is NULL", who);
   if (l->dtype != MOE_F32 && l->dtype != MOE_BF16) return fail(MOE_ERR_INVALID_ARG, "%s: dtype %d unknown", who, l->dtype);
@@ -372,7 +388,7 @@ const char* moe_last_error(void) { return g_last_error; }
 moe_status moe_gate_workspace_size(const moe_gate_params* p, size_t* bytes) {
   if (!bytes) return fail(MOE_ERR_INVALID_ARG, "bytes is NULL");
   CHECK(check_gate_params(p));
-  *bytes = gate_workspace_bytes(p);
+  *bytes = std::max(gate_workspace_bytes(p), gate_split_bytes(p));
   return ok();
 }
 
@@ -459,53 +475,55 @@ moe_status gate_call(const char* who, bool noalloc, const moe_gate_params* p, co
   int32_t* hist = static_cast<int32_t*>(workspace);
   hipError_t err;
 
-  RouteArgs fused{};
-  fused.S = p->S; fused.d = p->d; fused.E = p->E; fused.k = p->k; fused.nb = nb;
-  fused.kind = p->kind; fused.normalize = p->normalize; fused.logits_in = 0; fused.dtype = p->dtype;
-  fused.x = x; fused.wg = wg; fused.bias = bias; fused.logits = logits;
-  fused.ids = ids; fused.weights = weights; fused.hist = hist;
-  fused.groups = p->groups; fused.temperature = p->temperature; fused.noise = noise;
-  if (gate_extended(p) && !p->logits_in && route_fuses_extended(fused)) {
-    // projection, noise, temperature and selection in one kernel: the final
-    // logits never leave it unless the caller asks for them
-    err = launch_route(fused, stream);
-    if (err != hipSuccess) return hip_fail(err, "moe_gate: route kernel launch");
-  } else if (gate_extended(p)) {
-    // raw logits (projected into the workspace, or given), then noise,
-    // temperature and selection in a kernel of their own
-    float* wsl = reinterpret_cast<float*>(static_cast<char*>(workspace) +
-                                          ((gate_hist_bytes(p) + 255) & ~static_cast<size_t>(255)));
-    const float* raw = logits;
-    float* fin = wsl;
-    if (!p->logits_in) {
-      // projection only: a one-choice top-k pass writes the logits; its ids,
-      // weights and histogram are overwritten below
-      RouteArgs ra{};
-      ra.S = p->S; ra.d = p->d; ra.E = p->E; ra.k = 1; ra.nb = nb;
-      ra.kind = MOE_GATE_TOPK; ra.normalize = 0; ra.logits_in = 0; ra.dtype = p->dtype;
-      ra.x = x; ra.wg = wg; ra.bias = bias; ra.logits = wsl;
-      ra.ids = ids; ra.weights = weights; ra.hist = hist;
-      err = launch_route(ra, stream);
-      if (err != hipSuccess) return hip_fail(err, "moe_gate: route kernel launch");
-      raw = wsl;
-      fin = logits ? logits : wsl;
-    }
-    SelectArgs sel{};
-    sel.S = p->S; sel.E = p->E; sel.k = p->k; sel.nb = nb; sel.kind = p->kind; sel.normalize = p->normalize;
-    sel.groups = p->groups; sel.temperature = p->temperature;
-    sel.raw = raw; sel.noise = noise; sel.fin = fin; sel.ids = ids; sel.weights = weights; sel.hist = hist;
-    err = launch_select_ext(sel, stream);
+  // workspace past the histogram: partial or final logits
+  float* wsl = reinterpret_cast<float*>(static_cast<char*>(workspace) +
+                                        ((gate_hist_bytes(p) + 255) & ~static_cast<size_t>(255)));
+  SelectArgs sel{};
+  sel.S = p->S; sel.E = p->E; sel.k = p->k; sel.nb = nb; sel.kind = p->kind; sel.normalize = p->normalize;
+  sel.groups = p->groups; sel.temperature = p->temperature;
+  sel.planes = 1; sel.noise = noise; sel.ids = ids; sel.weights = weights; sel.hist = hist;
+  RouteArgs ra{};
+  ra.S = p->S; ra.d = p->d; ra.E = p->E; ra.k = p->k; ra.nb = nb;
+  ra.kind = p->kind; ra.normalize = p->normalize; ra.dtype = p->dtype;
+  ra.hash_seed = p->hash_seed;
+  ra.x = x; ra.wg = wg; ra.bias = bias; ra.token_ids = token_ids; ra.logits = logits;
+  ra.hash_table = hash_table; ra.hash_vocab = p->hash_vocab;
+  ra.ids = ids; ra.weights = weights; ra.hist = hist;
+  ra.groups = p->groups; ra.temperature = p->temperature; ra.noise = noise;
+  const TileSplit split = gate_split(p);
+  ra.zsplit = split.z; ra.zcols = split.cols;
+  if (p->logits_in) {
+    // past kSelectTileE experts the selection reads final logits from memory:
+    // the given ones, or those it first writes to the workspace
+    sel.raw = logits;
+    sel.fin = p->E <= kSelectTileE ? nullptr : p->temperature > 0.f ? wsl : logits;
+    err = launch_select_rows(sel, stream);
     if (err != hipSuccess) return hip_fail(err, "moe_gate: selection kernel launch");
-  } else {
-    RouteArgs ra{};
-    ra.S = p->S; ra.d = p->d; ra.E = p->E; ra.k = p->k; ra.nb = nb;
-    ra.kind = p->kind; ra.normalize = p->normalize; ra.logits_in = p->logits_in; ra.dtype = p->dtype;
-    ra.hash_seed = p->hash_seed;
-    ra.x = x; ra.wg = wg; ra.bias = bias; ra.token_ids = token_ids; ra.logits = logits;
-    ra.hash_table = hash_table; ra.hash_vocab = p->hash_vocab;
-    ra.ids = ids; ra.weights = weights; ra.hist = hist;
+  } else if (split.z > 1 && route_splits(ra) && workspace_bytes >= gate_split_bytes(p)) {
+    // K ranges over blocks, then their sum and the selection
+    ra.part = wsl;
     err = launch_route(ra, stream);
     if (err != hipSuccess) return hip_fail(err, "moe_gate: route kernel launch");
+    sel.planes = split.z; sel.raw = wsl; sel.bias = bias; sel.fin = logits;
+    err = launch_select_rows(sel, stream);
+    if (err != hipSuccess) return hip_fail(err, "moe_gate: selection kernel launch");
+  } else if (!gate_extended(p) || route_fuses_extended(ra)) {
+    // projection, noise, temperature and selection in one kernel: the final
+    // logits never leave it unless the caller asks for them
+    err = launch_route(ra, stream);
+    if (err != hipSuccess) return hip_fail(err, "moe_gate: route kernel launch");
+  } else {
+    // projection only: a one-choice top-k pass writes the logits (its ids,
+    // weights and histogram are overwritten below), then noise, temperature and
+    // selection in a kernel of their own
+    ra.k = 1; ra.kind = MOE_GATE_TOPK; ra.normalize = 0; ra.groups = 0; ra.temperature = 0.f; ra.noise = nullptr;
+    ra.logits = wsl;
+    err = launch_route(ra, stream);
+    if (err != hipSuccess) return hip_fail(err, "moe_gate: route kernel launch");
+    sel.raw = wsl;
+    sel.fin = logits ? logits : wsl;
+    err = launch_select_rows(sel, stream);
+    if (err != hipSuccess) return hip_fail(err, "moe_gate: selection kernel launch");
   }
 
   ScanArgs sa{};
@@ -691,9 +709,10 @@ moe_status base_gate_run(const char* who, const moe_base_params* p, const void* 
     // weights and histogram are overwritten by the auction's outputs
     RouteArgs ra{};
     ra.S = p->S; ra.d = p->d; ra.E = p->E; ra.k = 1; ra.nb = nb;
-    ra.kind = MOE_GATE_TOPK; ra.normalize = 0; ra.logits_in = 0; ra.dtype = p->dtype;
+    ra.kind = MOE_GATE_TOPK; ra.normalize = 0; ra.dtype = p->dtype;
     ra.x = x; ra.wg = wg; ra.bias = bias; ra.logits = out;
     ra.ids = ids; ra.weights = weights; ra.hist = hist;
+    ra.zsplit = 1; ra.zcols = p->d;
     if (p->S > 0) {
       err = launch_route(ra, stream);
       if (err != hipSuccess) return hip_fail(err, "moe_base_gate: route kernel launch");

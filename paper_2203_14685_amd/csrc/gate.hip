@@ -2,21 +2,21 @@
 // expert selection) and the capacity rule of Sec. 3.1 (each expert keeps at
 // most C assignments, handed out rank-major then in token order).
 //
-// Three launches, all on the caller's stream:
-//   route   logits (the projection x.W of Eq. 1, or read from the caller),
-//           streaming selection (top-k list, per-group top-1, or hash),
-//           softmax weights, and for every 64-token "wave block" a histogram of
-//           its (rank, expert) pairs.  Five variants:
-//             route_mfma_rs_kernel  bf16, W held in registers (E up to 128,
-//                                d 512..2048, d * E up to 128 K):
-//                                persistent, projection on
-//                                v_mfma_f32_16x16x32_bf16;
-//             route_mfma_ph_kernel  bf16, E in {16, 32, 64, 128}, d a multiple
-//                                of 512: persistent, W^T staged in LDS per
-//                                128 KB K phase;
-//             route_mfma_kernel  other bf16 shapes with E a multiple of 16 up
-//                                to 128: W staged through LDS per K chunk;
-//             route_valu_kernel  any dtype/shape: one thread per token;
+// Three launches (four with a split projection), all on the caller's stream:
+//   route   logits (the projection x.W of Eq. 1), selection (top-k list,
+//           per-group top-1, hierarchical top-k, or hash), softmax weights, and
+//           for every 64-token "wave block" a histogram of its (rank, expert)
+//           pairs.  Variants:
+//             route_mfma_rs_kernel  bf16, W held in registers (E in {16, 32, 64,
+//                                128}, d in {512, 1024, 2048}, d * E up to
+//                                128 K): persistent;
+//             route_tile_bf16_kernel, route_tile_f32_kernel  any E up to 256 and
+//                                any d: x and W staged per K stage; batches that
+//                                leave CUs idle split K over blocks, and
+//                                select_rows_kernel adds the partial logits and
+//                                selects (it also serves given logits);
+//             route_valu_kernel  more experts, or W not 16-byte aligned: one
+//                                thread per token;
 //             route_hash_kernel  the hash gate (no projection).
 //   scan    one block per expert: exclusive scan of that expert's histogram
 //           over (rank, wave block) -> first slot of each run; demand, counts;
@@ -63,96 +63,6 @@ __global__ __launch_bounds__(kBlock) void route_hash_kernel(RouteArgs a) {
   }
   const int wb = blockIdx.x * kWavesPerBlock + w;
   wave_block_hist(hist_lds + w * a.E, wb < a.nb, s, valid, wb, a);
-}
-
-// ---------------------------------------------------------------- selection on final logits
-constexpr int kSelTileE = 128;  // up to this many experts the block's logits are kept in LDS
-
-// One block per 64-token wave block, P lanes per token select on the block's
-// final logits.
-template <int P, int KMAX, int MODE>  // MODE: 0 top-k, 1 kTop1, 3 hierarchical top-k
-__global__ __launch_bounds__(kWave * P) void select_ext_kernel(SelectArgs a) {
-  extern __shared__ int hist_lds[];  // [k][E], then (E <= kSelTileE) the block's logits [64][E + 1]
-  constexpr int kThreads = kWave * P;
-  const int t = threadIdx.x / P, j = threadIdx.x % P;
-  const int64_t s = static_cast<int64_t>(blockIdx.x) * kWave + t;
-  const bool valid = s < a.S;
-  const int E = a.E;
-  for (int i = threadIdx.x; i < a.k * E; i += kThreads) hist_lds[i] = 0;
-  const bool use_tile = E <= kSelTileE;
-  float* tile = reinterpret_cast<float*>(hist_lds + a.k * E);
-  const bool transform = a.temperature > 0.f || a.fin != a.raw;
-  // the block's rows are one contiguous piece of [S, E]: a flat, coalesced pass
-  // makes the final logits ((raw + noise) / temperature, or raw), stores them
-  // when asked and keeps them in LDS; four loads are issued before their stores
-  if (transform || use_tile) {
-    const int64_t base = static_cast<int64_t>(blockIdx.x) * kWave * E;
-    const int64_t rows = min(static_cast<int64_t>(kWave), a.S - static_cast<int64_t>(blockIdx.x) * kWave);
-    const int n = static_cast<int>(rows) * E;
-    for (int f0 = threadIdx.x; f0 < n; f0 += 4 * kThreads) {
-      float v[4], g[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int f = f0 + u * kThreads;
-        v[u] = f < n ? a.raw[base + f] : 0.f;
-        g[u] = (f < n && a.noise) ? a.noise[base + f] : 0.f;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int f = f0 + u * kThreads;
-        if (f < n) {
-          float val = v[u];
-          if (a.temperature > 0.f) val = (a.noise ? val + g[u] : val) / a.temperature;
-          if (transform) a.fin[base + f] = val;
-          if (use_tile) tile[(f / E) * (E + 1) + f % E] = val;
-        }
-      }
-    }
-  }
-  __syncthreads();
-  // invalid tokens select on row 0 (their results are not written)
-  const float* lrow = use_tile ? tile + (valid ? t : 0) * (E + 1) : a.fin + (valid ? s : 0) * E;
-  if constexpr (MODE == 3) {
-    select_token_htopk<P, KMAX>(lrow, E, a.k, E / a.groups, a.normalize, j, valid, a.ids + s * a.k,
-                                a.weights + s * a.k, hist_lds);
-  } else {
-    select_token<P, KMAX, MODE == 1>(lrow, E, a.k, a.normalize, j, valid, a.ids + s * a.k, a.weights + s * a.k,
-                                     hist_lds);
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < a.k * E; i += kThreads)
-    a.hist[static_cast<int64_t>(i) * a.nb + blockIdx.x] = hist_lds[i];
-}
-
-template <int P, int KMAX, int MODE>
-static hipError_t launch_sel_t(const SelectArgs& a, hipStream_t st) {
-  const size_t tile = a.E <= kSelTileE ? static_cast<size_t>(kWave) * (a.E + 1) * sizeof(float) : 0;
-  select_ext_kernel<P, KMAX, MODE><<<dim3(static_cast<unsigned>(a.nb)), dim3(kWave * P),
-                                     static_cast<size_t>(a.k) * a.E * sizeof(int) + tile, st>>>(a);
-  return hipGetLastError();
-}
-
-template <int P, int MODE>
-static hipError_t launch_sel_m(const SelectArgs& a, hipStream_t st) {
-  if (MODE == 1 || a.k == 1) return launch_sel_t<P, 1, MODE>(a, st);
-  if (a.k == 2) return launch_sel_t<P, 2, MODE>(a, st);
-  if (a.k <= 4) return launch_sel_t<P, 4, MODE>(a, st);
-  return launch_sel_t<P, 8, MODE>(a, st);
-}
-
-template <int P>
-static hipError_t launch_sel_p(const SelectArgs& a, hipStream_t st) {
-  if (a.kind == 1) return launch_sel_m<P, 1>(a, st);
-  if (a.kind == 3) return launch_sel_m<P, 3>(a, st);
-  return launch_sel_m<P, 0>(a, st);
-}
-
-hipError_t launch_select_ext(const SelectArgs& a, hipStream_t st) {
-  if (a.nb == 0) return hipSuccess;
-  // 4 lanes per token when they split the experts evenly (and, for kTop1,
-  // agree with the groups), else one
-  const bool four = a.E % 4 == 0 && (a.kind != 1 || 4 % a.k == 0 || a.k % 4 == 0);
-  return four ? launch_sel_p<4>(a, st) : launch_sel_p<1>(a, st);
 }
 
 // ---------------------------------------------------------------- scan kernel
@@ -368,6 +278,15 @@ int device_cu_count() {
   return n;
 }
 
+#ifndef HETUMOE_ROUTE_VALU_ONLY
+static bool route_uses_tile(const RouteArgs& a) { return route_uses_tile_bf16(a) || route_uses_tile_f32(a); }
+bool route_splits(const RouteArgs& a) { return !route_uses_mfma_rs(a) && route_uses_tile(a); }
+bool route_fuses_extended(const RouteArgs& a) { return route_uses_mfma_rs(a) || route_uses_tile(a); }
+#else
+bool route_splits(const RouteArgs&) { return false; }
+bool route_fuses_extended(const RouteArgs&) { return false; }
+#endif
+
 hipError_t launch_route(const RouteArgs& a, hipStream_t st) {
   if (a.nb == 0) return hipSuccess;
   if (a.kind == 2) {
@@ -377,14 +296,12 @@ hipError_t launch_route(const RouteArgs& a, hipStream_t st) {
   }
 #ifndef HETUMOE_ROUTE_VALU_ONLY
   // matrix-core projections (a build with HETUMOE_ROUTE_VALU_ONLY defined, used
-  // only to time the vector-ALU routes against them, skips these)
+  // only to time the vector-ALU route against them, skips these)
   if (route_uses_mfma_rs(a)) return launch_route_mfma_rs(a, device_cu_count(), st);
-  if (route_uses_mfma_ph(a)) return launch_route_mfma_ph(a, device_cu_count(), st);
-  if (route_uses_mfma(a)) return launch_route_mfma(a, st);
+  if (route_uses_tile_bf16(a)) return launch_route_tile_bf16(a, st);
+  if (route_uses_tile_f32(a)) return launch_route_tile_f32(a, st);
 #endif
-  // with logits given, the element type of x and wg is irrelevant
-  if (a.dtype == 1 && !a.logits_in) return launch_route_valu_bf16(a, st);
-  return launch_route_valu_f32(a, st);
+  return a.dtype == 1 ? launch_route_valu_bf16(a, st) : launch_route_valu_f32(a, st);
 }
 
 hipError_t launch_scan(const ScanArgs& a, hipStream_t st) {

@@ -8,7 +8,7 @@ namespace hetumoe {
 
 struct RouteArgs {
   int S, d, E, k, nb;
-  int kind, normalize, logits_in, dtype;
+  int kind, normalize, dtype;
   uint64_t hash_seed;
   const void* x;            // [S, d]
   const void* wg;           // [d, E]
@@ -16,16 +16,22 @@ struct RouteArgs {
   const int32_t* token_ids; // [S] (hash)
   const int32_t* hash_table; // [hash_vocab] (hash with a table) or null
   int hash_vocab;
-  float* logits;            // [S, E]: input (logits_in), output, or null
+  float* logits;            // [S, E] output or null
   int32_t* ids;             // [S, k]
   float* weights;           // [S, k]
   int32_t* hist;            // [k, E, nb] workspace (nb = 64-token wave blocks)
-  // the extended gates, for a route kernel that selects on final logits itself
-  // (route_fuses_extended): kind 3 is the hierarchical top-k over `groups`
+  // the extended gates, for the route kernels that select on final logits
+  // themselves (route_fuses_extended): kind 3 is the hierarchical top-k over `groups`
   // groups; temperature > 0 selects on (logits + noise) / temperature
   int groups;
   float temperature;
   const float* noise;       // [S, E] or null
+  // tiled routes: K split into zsplit ranges of zcols columns (route_tile_split).
+  // With part, a block takes one range and writes its sums there, [zsplit, S, E],
+  // and the selection runs in a launch of its own; without, one block takes all
+  // ranges and adds them in the same order.
+  int zsplit, zcols;
+  float* part;
 };
 
 struct ScanArgs {
@@ -60,33 +66,46 @@ struct RowArgs {
 
 hipError_t launch_route(const RouteArgs& a, hipStream_t st);
 
-// Selection on logits that first take noise and a temperature (Dense-To-Sparse)
-// and/or the hierarchical top-k: one block per 64-token wave block.
+// Selection on logits in memory: given ones, or `planes` partial sums of a
+// projection, which are added in order before the bias; noise and temperature
+// (Dense-To-Sparse) follow.  One block per 64-token wave block.
 struct SelectArgs {
   int S, E, k, nb, kind, normalize, groups;
-  float temperature;       // > 0: fin = (raw + noise) / temperature; 0: fin = raw
-  const float* raw;        // [S, E] logits as projected (or given)
+  float temperature;       // > 0: (sum + noise) / temperature
+  int planes;              // partial sums of raw, S * E apart
+  const float* raw;        // [planes, S, E]
+  const float* bias;       // [E] or null
   const float* noise;      // [S, E] or null
-  float* fin;              // [S, E] logits the selection uses (may be raw itself)
+  float* fin;              // [S, E] final logits or null; required past kSelectTileE experts
+                           // unless they are raw itself
   int32_t* ids;            // [S, k]
   float* weights;          // [S, k]
   int32_t* hist;           // [k, E, nb]
 };
-hipError_t launch_select_ext(const SelectArgs& a, hipStream_t st);
+constexpr int kSelectTileE = 256;  // up to this many experts the block's logits are kept in LDS
+hipError_t launch_select_rows(const SelectArgs& a, hipStream_t st);
 hipError_t launch_route_valu_f32(const RouteArgs& a, hipStream_t st);
 hipError_t launch_route_valu_bf16(const RouteArgs& a, hipStream_t st);
-hipError_t launch_route_mfma(const RouteArgs& a, hipStream_t st);
-bool route_uses_mfma(const RouteArgs& a);
+hipError_t launch_route_tile_bf16(const RouteArgs& a, hipStream_t st);
+hipError_t launch_route_tile_f32(const RouteArgs& a, hipStream_t st);
+bool route_uses_tile_bf16(const RouteArgs& a);
+bool route_uses_tile_f32(const RouteArgs& a);
+// K ranges of the tiled routes: how many (1 unless the batch alone leaves CUs
+// idle) and how long.
+struct TileSplit {
+  int z, cols;
+};
+TileSplit route_tile_split(int S, int d, int E, int dtype);
 hipError_t launch_route_mfma_rs(const RouteArgs& a, int cus, hipStream_t st);
-hipError_t launch_route_mfma_ph(const RouteArgs& a, int cus, hipStream_t st);
-bool route_uses_mfma_ph(const RouteArgs& a);
 // Compute units of the current device (queried once per device).
 int device_cu_count();
 bool route_uses_mfma_rs(const RouteArgs& a);
-// True when the register-resident route kernel takes this projection: it then
-// also applies the noise and temperature and the hierarchical top-k itself, so
-// the extended gates need no logits round trip.
+// True when a matrix-core route kernel takes this projection: it then also
+// applies the noise and temperature and the hierarchical top-k itself, so the
+// extended gates need no logits round trip.
 bool route_fuses_extended(const RouteArgs& a);
+// True when launch_route can take one K range per block (RouteArgs::part).
+bool route_splits(const RouteArgs& a);
 hipError_t launch_scan(const ScanArgs& a, hipStream_t st);
 hipError_t launch_assign(const AssignArgs& a, hipStream_t st);
 // Scan and assign, in one launch when the histogram is small (the offsets then

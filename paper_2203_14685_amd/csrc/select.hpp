@@ -160,66 +160,10 @@ struct Ktop1State {
   }
 };
 
-// ---------------------------------------------------------------- parallel selection
-// Selection for one token by P consecutive lanes of a wave (lane j = 0..P-1 of
-// the token streams experts [j*E/P, (j+1)*E/P) of its logit row, then the lanes
-// merge by butterfly shuffles).  All P lanes must call this together.  The lane
-// that writes an (id, weight) pair also counts it in hist_lds[r][id] (LDS).
-template <int P, int KMAX, bool KTOP1>
-__device__ __forceinline__ void select_token(const float* lrow, int E, int k, int normalize, int j, bool valid,
-                                             int32_t* ids, float* weights, int* hist_lds) {
-  const int slice = E / P;
-  const int e0 = j * slice;
-  if constexpr (!KTOP1) {
-    TopkState<KMAX> tk;
-    tk.init();
-    for (int e = 0; e < slice; ++e) tk.push(lrow[e0 + e], e0 + e);
-#pragma unroll
-    for (int msk = 1; msk < P; msk <<= 1) tk.merge_xor(msk);
-    if (valid && j == 0) {
-      tk.finish(k, normalize, ids, weights);
-#pragma unroll
-      for (int r = 0; r < KMAX; ++r)
-        if (r < k) atomicAdd(&hist_lds[r * E + tk.ti[r]], 1);
-    }
-  } else {
-    const int G = E / k;
-    if (P % k == 0) {
-      // L = P / k lanes per group; lane j's experts lie in group j / L
-      const int L = P / k;
-      GroupBest gb;
-      gb.init();
-      for (int e = 0; e < slice; ++e) gb.push(lrow[e0 + e], e0 + e);
-      for (int msk = 1; msk < L; msk <<= 1) gb.merge_xor(msk);
-      if (valid && j % L == 0) {
-        const int grp = j / L;
-        ids[grp] = gb.bi;
-        weights[grp] = 1.f / gb.gsum;
-        atomicAdd(&hist_lds[grp * E + gb.bi], 1);
-      }
-    } else if (k % P == 0) {
-      // each lane's experts are k / P whole groups
-      if (valid) {
-        for (int grp = e0 / G; grp < (e0 + slice) / G; ++grp) {
-          GroupBest gb;
-          gb.init();
-          for (int e = grp * G; e < (grp + 1) * G; ++e) gb.push(lrow[e], e);
-          ids[grp] = gb.bi;
-          weights[grp] = 1.f / gb.gsum;
-          atomicAdd(&hist_lds[grp * E + gb.bi], 1);
-        }
-      }
-    } else if (valid && j == 0) {
-      Ktop1State kt;
-      kt.init(G);
-      for (int e = 0; e < E; ++e) kt.push(lrow[e], e, ids, weights);
-      for (int r = 0; r < k; ++r) atomicAdd(&hist_lds[r * E + ids[r]], 1);
-    }
-  }
-}
-
 // ---------------------------------------------------------------- selection on a compile-time slice
-// The same selections for kernels that know E at compile time: lane j's SL =
+// Selection for one token by P consecutive lanes of a wave, for kernels that know
+// E at compile time (all P lanes must call this together; the lane that writes
+// an (id, weight) pair also counts it in hist_lds[r][id]): lane j's SL =
 // E / P logits are read from LDS at once (`lslice` points at them; 8-byte
 // aligned for SL = 2, 16-byte aligned from SL = 4 on) and held in registers;
 // the maximum comes first and the softmax sum of the slice relative to it
@@ -287,8 +231,9 @@ __device__ __forceinline__ void select_token_c(const float* lrow, int k, int nor
       for (int r = 0; r < KMAX; ++r)
         if (r < k) atomicAdd(&hist_lds[r * E + tk.ti[r]], 1);
     }
-  } else if (P % k == 0) {
-    // L = P / k lanes per group; lane j's experts lie in group j / L
+  } else {
+    // k divides E, a power of two, and so P: L = P / k lanes per group; lane j's
+    // experts lie in group j / L
     const int L = P / k;
     float v[SL];
     load_slice<SL>(lrow + e0, v);
@@ -309,8 +254,155 @@ __device__ __forceinline__ void select_token_c(const float* lrow, int k, int nor
       weights[grp] = 1.f / gb.gsum;
       atomicAdd(&hist_lds[grp * E + gb.bi], 1);
     }
+  }
+}
+
+// ---------------------------------------------------------------- selection on a row of any length
+// One token by P consecutive lanes: lane j takes experts j, j + P, ... (the
+// lanes read neighbouring LDS words, and P need not divide E) and keeps the KMAX
+// best of them sorted; then, k times, the lanes take the best head of their
+// lists and its lane drops it.  Logits are compared as integer keys of the same
+// order (-0 as +0, NaN below -inf, an empty entry below all): one med3, one
+// compare and two selects per entry and inserted logit, where float comparisons
+// with an index tie-break took about 14, and a max and a min over the lanes per
+// choice in place of sorted-list merges.
+constexpr int kKeyEmpty = static_cast<int>(0x80000000u);
+constexpr int kKeyNan = kKeyEmpty + 1;
+
+__device__ __forceinline__ int logit_key(float v) {
+  const int b = __float_as_int(v + 0.f);  // -0 becomes +0
+  return v != v ? kKeyNan : b ^ ((b >> 31) & 0x7fffffff);
+}
+__device__ __forceinline__ float key_logit(int key) { return __int_as_float(key ^ ((key >> 31) & 0x7fffffff)); }
+
+struct OpMinI {
+  __device__ __forceinline__ int operator()(int a, int b) const { return a < b ? a : b; }
+};
+
+// The KMAX best of a lane's logits, best first; equal keys in expert order
+// (experts come in increasing order, and an equal key displaces nothing).
+template <int KMAX>
+struct KeyList {
+  int key[KMAX], id[KMAX];
+  __device__ __forceinline__ void init() {
+#pragma unroll
+    for (int i = 0; i < KMAX; ++i) { key[i] = kKeyEmpty; id[i] = kEmpty; }
+  }
+  __device__ __forceinline__ void insert(int v, int e) {
+    bool up = v > key[KMAX - 1];  // v goes to entry i or above
+#pragma unroll
+    for (int i = KMAX - 1; i > 0; --i) {
+      const bool above = v > key[i - 1];
+      id[i] = above ? id[i - 1] : up ? e : id[i];
+      key[i] = max(min(key[i - 1], v), key[i]);  // the middle one of the three
+      up = above;
+    }
+    id[0] = up ? e : id[0];
+    key[0] = max(key[0], v);
+  }
+  // lane j of P takes experts lo + j, lo + j + P, ... below hi
+  template <int P>
+  __device__ __forceinline__ void scan(const float* lrow, int lo, int hi, int j) {
+    init();
+    for (int e = lo + j; e < hi; e += 4 * P) {
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = lrow[min(e + u * P, hi - 1)];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) insert(e + u * P < hi ? logit_key(v[u]) : kKeyEmpty, e + u * P);
+    }
+  }
+  // The best of the P lanes' first entries, dropped from its list.  LEFT: the
+  // entries still wanted after it.
+  template <int P, int LEFT>
+  __device__ __forceinline__ void pop(int& best, int& expert) {
+    best = group_reduce<P>(key[0], OpMaxI());
+    expert = group_reduce<P>(key[0] == best ? id[0] : kEmpty, OpMinI());
+    const bool mine = id[0] == expert;
+#pragma unroll
+    for (int i = 0; i < LEFT; ++i) {  // LEFT < KMAX
+      key[i] = mine ? key[i + 1] : key[i];
+      id[i] = mine ? id[i + 1] : id[i];
+    }
+  }
+};
+
+// Sum of exp(logit - top) over the experts [lo, hi), by all P lanes.
+template <int P>
+__device__ __forceinline__ float row_expsum(const float* lrow, int lo, int hi, int j, float top) {
+  float s = 0.f;
+  for (int e = lo + j; e < hi; e += 4 * P) {
+    float v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = lrow[min(e + u * P, hi - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) s += e + u * P < hi ? __expf(v[u] - top) : 0.f;
+  }
+  return group_reduce<P>(s, OpAdd());
+}
+
+// All KMAX best of the P lanes, in order, on every lane.
+template <int P, int KMAX, int R>
+__device__ __forceinline__ void pop_all(KeyList<KMAX>& list, int (&key)[KMAX], int (&id)[KMAX]) {
+  list.template pop<P, KMAX - 1 - R>(key[R], id[R]);
+  if constexpr (R + 1 < KMAX) pop_all<P, KMAX, R + 1>(list, key, id);
+}
+
+// MODE: 0 top-k, 1 kTop1, 3 hierarchical top-k.  All P lanes call this
+// together.  Choice r is written by lane r % P, which also counts it in
+// hist_lds[r][id].
+template <int P, int KMAX, int MODE>
+__device__ __forceinline__ void select_row(const float* lrow, int E, int k, int groups, int normalize, int j,
+                                           bool valid, int32_t* ids, float* weights, int* hist_lds) {
+  if constexpr (MODE == 1) {
+    const int G = E / k;
+    for (int grp = 0; grp < k; ++grp) {
+      const int lo = grp * G, hi = lo + G;
+      KeyList<1> best;
+      best.template scan<P>(lrow, lo, hi, j);
+      int key, id;
+      best.template pop<P, 0>(key, id);
+      const float z = row_expsum<P>(lrow, lo, hi, j, key_logit(key));
+      if (valid && j == grp % P) {
+        ids[grp] = id;
+        weights[grp] = 1.f / z;
+        atomicAdd(&hist_lds[grp * E + id], 1);
+      }
+    }
   } else {
-    select_token<P, KMAX, true>(lrow, E, k, normalize, j, valid, ids, weights, hist_lds);
+    int lo = 0, hi = E;
+    if constexpr (MODE == 3) {
+      // the group of the best expert over all
+      KeyList<1> first;
+      first.template scan<P>(lrow, 0, E, j);
+      int key, id;
+      first.template pop<P, 0>(key, id);
+      const int Gs = E / groups;
+      lo = id / Gs * Gs;
+      hi = lo + Gs;
+    }
+    KeyList<KMAX> list;
+    list.template scan<P>(lrow, lo, hi, j);
+    int key[KMAX], id[KMAX];
+    pop_all<P, KMAX, 0>(list, key, id);
+    const float top = key_logit(key[0]);
+    float z = 0.f;
+    if (normalize) {
+#pragma unroll
+      for (int r = 0; r < KMAX; ++r)
+        if (r < k) z += __expf(key_logit(key[r]) - top);
+    } else {
+      z = row_expsum<P>(lrow, 0, E, j, top);
+    }
+    const float inv = 1.f / z;
+#pragma unroll
+    for (int r = 0; r < KMAX; ++r) {
+      if (r < k && valid && j == r % P) {
+        ids[r] = id[r];
+        weights[r] = (r == 0 ? 1.f : __expf(key_logit(key[r]) - top)) * inv;
+        atomicAdd(&hist_lds[r * E + id[r]], 1);
+      }
+    }
   }
 }
 
@@ -319,42 +411,10 @@ __device__ __forceinline__ void select_token_c(const float* lrow, int k, int nor
 // Every wave of the block calls this (it synchronises the block); `active` waves
 // own a wave block, `s` is the calling lane's token.  The ids are read back from
 // global memory, where the same thread wrote them.
-// Hierarchical top-k for one token by P consecutive lanes (Sec. 3.1, H Topk):
-// the best expert over all E (with the full softmax sum), its group of Gs
-// contiguous experts, then the k best experts of that group.  Weights: softmax
-// over the k chosen (normalize) or the full softmax at each of them.
-template <int P, int KMAX>
-__device__ __forceinline__ void select_token_htopk(const float* lrow, int E, int k, int Gs, int normalize, int j,
-                                                   bool valid, int32_t* ids, float* weights, int* hist_lds) {
-  const int slice = E / P;
-  const int e0 = j * slice;
-  TopkState<1> t1;
-  t1.init();
-  for (int e = 0; e < slice; ++e) t1.push(lrow[e0 + e], e0 + e);
-#pragma unroll
-  for (int msk = 1; msk < P; msk <<= 1) t1.merge_xor(msk);
-  const int best = t1.ti[0] == kEmpty ? 0 : t1.ti[0];
-  const int lo = (best / Gs) * Gs, hi = lo + Gs;
-  TopkState<KMAX> tk;
-  tk.init();
-  for (int e = 0; e < slice; ++e) {
-    const int ee = e0 + e;
-    if (ee >= lo && ee < hi) tk.insert(lrow[ee], ee);
-  }
-#pragma unroll
-  for (int msk = 1; msk < P; msk <<= 1) tk.merge_xor(msk);
-  // the group holds the overall best: the full softmax sum relative to it
-  tk.m = t1.m;
-  tk.ssum = t1.ssum;
-  if (valid && j == 0) {
-    tk.finish(k, normalize, ids, weights);
-#pragma unroll
-    for (int r = 0; r < KMAX; ++r)
-      if (r < k) atomicAdd(&hist_lds[r * E + tk.ti[r]], 1);
-  }
-}
-
-// Hierarchical top-k on a compile-time slice (see select_token_c).
+// Hierarchical top-k (Sec. 3.1, H Topk) on a compile-time slice: the best expert
+// over all E (with the full softmax sum), its group of Gs contiguous experts,
+// then the k best experts of that group.  Weights: softmax over the k chosen
+// (normalize) or the full softmax at each of them.
 template <int P, int KMAX, int SL>
 __device__ __forceinline__ void select_token_htopk_c(const float* lrow, int k, int Gs, int normalize, int j,
                                                      bool valid, int32_t* ids, float* weights, int* hist_lds) {
