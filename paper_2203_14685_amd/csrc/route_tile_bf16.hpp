@@ -14,7 +14,9 @@ namespace hetumoe {
 // fragments are 16-byte LDS reads of x, B fragments (8 consecutive K of one
 // expert) transpose reads of W.  The next stage is loaded into registers while
 // the current one is multiplied; columns past d and rows past the batch come
-// from outside the buffer resources and are zeros.  Experts past E hold
+// from outside the buffer resources and are zeros.  Each stage is summed on its
+// own and then added to the running sum, so rounding grows with the stages, not
+// with d / 32.  Experts past E hold
 // whatever LDS held: their columns are never read.
 template <int NT, int WM, int WN, int KC, int DEPTH, int KMAX, int MODE>
 __global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs a) {
@@ -104,10 +106,15 @@ __global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs 
     }
   };
 
-  f32x4 acc[MT][NTW], sum[MT][NTW];
+  f32x4 rsum[MT][NTW], sum[MT][NTW];
   auto multiply = [&](int buf) {
     const uint16_t* xs = reinterpret_cast<const uint16_t*>(raw + buf * kStage);
     const uint16_t* ws = xs + kTileTok * LDX;
+    f32x4 acc[MT][NTW];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int nt = 0; nt < NTW; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ks = 0; ks < KC / 32; ++ks) {
       u32x4 av[MT];
@@ -129,6 +136,10 @@ __global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs 
                                                                 __builtin_bit_cast(bf16x8, bv), acc[mt][nt], 0, 0, 0);
       }
     }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int nt = 0; nt < NTW; ++nt) rsum[mt][nt] += acc[mt][nt];
   };
 
   // Stage s + 1 goes to LDS and stage s + 1 + DEPTH is requested while stage s
@@ -142,7 +153,7 @@ __global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs 
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-      for (int nt = 0; nt < NTW; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int nt = 0; nt < NTW; ++nt) rsum[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int q = 0; q < DEPTH; ++q) load(xq[q], wq[q], k0 + q * KC, kend);
     stage(xq[0], wq[0], 0);
@@ -165,7 +176,7 @@ __global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs 
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-      for (int nt = 0; nt < NTW; ++nt) sum[mt][nt] = z == z0 ? acc[mt][nt] : sum[mt][nt] + acc[mt][nt];
+      for (int nt = 0; nt < NTW; ++nt) sum[mt][nt] = z == z0 ? rsum[mt][nt] : sum[mt][nt] + rsum[mt][nt];
   }
   if constexpr (MODE == kTilePart) {
     float* plane = tile_plane(a);
