@@ -15,7 +15,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libhetumoe.so")
 
-SOURCES = ["base.hip", "gate_bwd.hip", "route_valu_f32.hip", "route_valu_bf16.hip", "route_mfma_rs.hip",
+SOURCES = ["base.hip", "gate_bwd.hip", "gate_bwd_tile.hip", "route_valu_f32.hip", "route_valu_bf16.hip", "route_mfma_rs.hip",
            "route_tile_bf16_small.hip", "route_tile_bf16_large.hip", "route_tile_f32.hip", "select_rows.hip",
            "gate.hip", "layout.hip", "capi.hip"]
 

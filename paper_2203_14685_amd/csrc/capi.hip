@@ -205,8 +205,14 @@ GateBwdPlan plan_gate_bwd(const moe_gate_bwd_params* p) {
   // blocks of 256 columns, two per CU, or 1024 vector blocks of 64), each range
   // a whole number of 64-token blocks; matrix-core ranges keep at least 4 of
   // them where the batch allows, so that each block pipelines several chunks
-  const int64_t per_split = g.mfma ? (p->d + 255) / 256 : ((p->d + 63) / 64) * ((p->E + 63) / 64);
-  const int64_t target = g.mfma ? 512 : 1024;
+  // tiled bf16 shapes: one block of 128 columns and 8 waves per CU past 128
+  // experts (8192 x 4096, E = 256: 118 us at 128 blocks, see the kernel at 256),
+  // else of 256 columns
+  const bool tiled = !g.mfma && p->dtype == MOE_BF16 && gate_bwd_tile_shape(p->E, p->d);
+  const int64_t per_split = g.mfma ? (p->d + 255) / 256
+                            : tiled ? (p->d + (p->E > 128 ? 127 : 255)) / (p->E > 128 ? 128 : 256)
+                                    : ((p->d + 63) / 64) * ((p->E + 63) / 64);
+  const int64_t target = g.mfma ? 512 : tiled ? (p->E > 64 ? 256 : 512) : 1024;
   int64_t ns = (target + per_split - 1) / per_split;
   if (g.mfma && ns > g.nb / 4) ns = g.nb / 4;
   if (ns > g.nb) ns = g.nb;
@@ -346,6 +352,9 @@ moe_status moe_gate_bwd(const moe_gate_bwd_params* p, const void* x, const void*
   a.mfma_dw = (g.mfma && dwg) ? 1 : 0;
   // the matrix-core dx reads W rows and dL with 16-byte loads
   a.mfma_dx = (g.mfma && dx && aligned(wg, 16) && (!dlogits || aligned(dlogits, 16))) ? 1 : 0;
+  // every other shape the tiled kernels take; dx reads W in 16-byte pieces
+  a.tile_dw = (dwg && !a.mfma_dw && gate_bwd_tile_shape(p->E, p->d)) ? 1 : 0;
+  a.tile_dx = (dx && !a.mfma_dx && gate_bwd_tile_shape(p->E, p->d) && aligned(wg, 16)) ? 1 : 0;
   a.s_pad = g.s_pad;
   // with dW wanted, its reduction launch also takes db and the balance loss
   a.sums_in_reduce = (dwg && p->E <= 64) ? 1 : 0;

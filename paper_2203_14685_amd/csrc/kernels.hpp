@@ -124,6 +124,7 @@ struct GateBwdArgs {
   float temperature;        // > 0: the logits are (L + noise) / temperature; gradients w.r.t. L
   int nsplit, split_tokens; // dW is summed over tokens in nsplit ranges of split_tokens (a multiple of 64)
   int mfma_dw, mfma_dx;     // matrix-core paths (bf16, E a multiple of 16 up to 128, d a multiple of 64)
+  int tile_dw, tile_dx;     // tiled matrix-core paths (gate_bwd_tile.hip)
   int sums_in_reduce;       // db, the softmax sums and the loss run as extra blocks of the dW reduction
   int64_t s_pad;            // row length of dlt: S rounded up to 64
   const void* x;            // [S, d]
@@ -149,6 +150,12 @@ struct GateBwdArgs {
 inline bool gate_bwd_mfma_shape(int dtype, int E, int d) {
   return dtype == 1 && E % 16 == 0 && E <= 128 && d % 64 == 0;
 }
+
+// Tiled matrix-core products: any other shape of up to 256 experts whose rows
+// and row groups the kernels address with 32-bit offsets.
+inline bool gate_bwd_tile_shape(int E, int d) { return E <= 256 && d <= (1 << 20); }
+void launch_dwg_tile(const GateBwdArgs& a, hipStream_t st);
+void launch_dx_tile(const GateBwdArgs& a, hipStream_t st);
 
 hipError_t launch_gate_bwd_dl(const GateBwdArgs& a, hipStream_t st);
 hipError_t launch_gate_bwd_dwg(const GateBwdArgs& a, hipStream_t st);
