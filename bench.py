@@ -28,7 +28,7 @@ OPS = ("gate", "dispatch", "combine", "combine_bwd", "dispatch_bwd")
 # struct's definition alone (the argument block the kernel reads)
 _LAYOUT_SRC = ("layout.hip", "common.hpp", "kernels.hpp:RowArgs")
 _GATE_SRC = ("gate.hip", "route_mfma_rs.hip", "route_tile.hpp", "route_tile_bf16.hpp", "route_tile_bf16_small.hip",
-             "route_tile_bf16_large.hip", "route_tile_f32.hip", "select_rows.hip", "route_valu.hpp", "route_valu_f32.hip",
+             "route_tile_bf16_large.hip", "route_tile_f32.hip", "select_rows.hip", "slots.hip", "route_valu.hpp", "route_valu_f32.hip",
              "route_valu_bf16.hip", "select.hpp", "common.hpp", "kernels.hpp:RouteArgs")
 OPS_KERNELS = ("dispatch", "combine", "combine_bwd", "dispatch_bwd", "gate")
 

@@ -17,7 +17,7 @@ LIB = os.path.join(PKG, "libhetumoe.so")
 
 SOURCES = ["base.hip", "gate_bwd.hip", "gate_bwd_tile.hip", "route_valu_f32.hip", "route_valu_bf16.hip", "route_mfma_rs.hip",
            "route_tile_bf16_small.hip", "route_tile_bf16_large.hip", "route_tile_f32.hip", "select_rows.hip",
-           "gate.hip", "layout.hip", "capi.hip"]
+           "gate.hip", "slots.hip", "layout.hip", "capi.hip"]
 
 # -packed-fp32-ops: no v_pk_{add,mul,fma}_f32 in generated code.
 HIPCC_FLAGS = [

@@ -1007,7 +1007,7 @@ __global__ __launch_bounds__(kBaseThreads) void base_tail_kernel(BaseArgs a, int
 }
 
 // ---------------------------------------------------------------- outputs
-// ids, weights (sigmoid of the score) and the wave-block histogram [E, nb]
+// ids, weights (sigmoid of the score) and the wave-block histogram [nb, E]
 // that the scan and assign kernels turn into slots
 // With `status` (the asynchronous form) the outputs are written whatever the
 // outcome, every token with a valid expert (its current one, else s mod E, so
@@ -1039,7 +1039,7 @@ __global__ __launch_bounds__(kBlock) void base_finish_kernel(BaseArgs a, int r, 
   if (valid) atomicAdd(&lds[e], 1);
   __syncthreads();
   if (wb < a.nb)
-    for (int i = lane; i < a.E; i += kWave) a.hist[static_cast<int64_t>(i) * a.nb + wb] = lds[i];
+    for (int i = lane; i < a.E; i += kWave) a.hist[static_cast<int64_t>(wb) * a.E + i] = lds[i];
   if (a.prices_out && blockIdx.x == 0)
     for (int i = tid; i < a.E; i += kBlock) a.prices_out[i] = a.price[i];
 }

@@ -103,7 +103,7 @@ bool gate_extended(const moe_gate_params* p) {
   return p->kind != MOE_GATE_HASH && (p->kind == MOE_GATE_HTOPK || p->temperature > 0.f);
 }
 
-// Workspace: the histogram, int32 [k, E, ceil(S/64)]; for the extended gates
+// Workspace: the histogram, int32 [ceil(S/64), k, E]; for the extended gates
 // also a logits buffer, fp32 [S, E], 256-byte aligned after the histogram.
 size_t gate_hist_bytes(const moe_gate_params* p) {
   const size_t n = static_cast<size_t>(p->k) * static_cast<size_t>(hist_blocks(p->S)) * static_cast<size_t>(p->E);
@@ -257,7 +257,7 @@ moe_status check_base_params(const moe_base_params* p) {
   return MOE_OK;
 }
 
-// Workspace of moe_base_gate, each piece 256-byte aligned: hist int32 [E, nb];
+// Workspace of moe_base_gate, each piece 256-byte aligned: hist int32 [nb, E];
 // logits fp32 [S, E] (only when projected); price fp64 [E]; hold_v fp64 [S];
 // hold_t, assign, bid_e int32 [S]; bid_v fp64 [S]; hold_n, bid_cnt int32 [E];
 // counts int32 [2]; the auction state [2]; range partials fp32 [3, 256].
@@ -535,14 +535,11 @@ moe_status gate_call(const char* who, bool noalloc, const moe_gate_params* p, co
     if (err != hipSuccess) return hip_fail(err, "moe_gate: selection kernel launch");
   }
 
-  ScanArgs sa{};
-  sa.E = p->E; sa.k = p->k; sa.nb = nb; sa.C = p->capacity;
-  sa.hist = hist; sa.counts = counts; sa.demand = demand; sa.slot_src = slot_src;
   AssignArgs aa{};
   aa.S = p->S; aa.E = p->E; aa.k = p->k; aa.nb = nb; aa.C = p->capacity;
-  aa.ids = ids; aa.offs = hist; aa.slots = slots; aa.slot_src = slot_src;
-  err = launch_scan_assign(sa, aa, stream);
-  if (err != hipSuccess) return hip_fail(err, "moe_gate: scan / assign kernel launch");
+  aa.ids = ids; aa.hist = hist; aa.counts = counts; aa.demand = demand; aa.slots = slots; aa.slot_src = slot_src;
+  err = launch_assign(aa, stream);
+  if (err != hipSuccess) return hip_fail(err, "moe_gate: assign kernel launch");
   return ok();
 }
 
@@ -758,14 +755,11 @@ moe_status base_gate_run(const char* who, const moe_base_params* p, const void* 
       return fail(MOE_ERR_NOT_CONVERGED, "%s: no balanced assignment after %d rounds of a phase", who, a.max_rounds);
   }
 
-  ScanArgs sa{};
-  sa.E = p->E; sa.k = 1; sa.nb = nb; sa.C = p->capacity;
-  sa.hist = hist; sa.counts = counts; sa.demand = nullptr; sa.slot_src = slot_src;
   AssignArgs aa{};
   aa.S = p->S; aa.E = p->E; aa.k = 1; aa.nb = nb; aa.C = p->capacity;
-  aa.ids = ids; aa.offs = hist; aa.slots = slots; aa.slot_src = slot_src;
-  err = launch_scan_assign(sa, aa, stream);
-  if (err != hipSuccess) return hip_fail(err, "moe_base_gate: scan / assign kernel launch");
+  aa.ids = ids; aa.hist = hist; aa.counts = counts; aa.demand = nullptr; aa.slots = slots; aa.slot_src = slot_src;
+  err = launch_assign(aa, stream);
+  if (err != hipSuccess) return hip_fail(err, "moe_base_gate: assign kernel launch");
   return ok();
 }
 

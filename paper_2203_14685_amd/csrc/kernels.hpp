@@ -19,7 +19,7 @@ struct RouteArgs {
   float* logits;            // [S, E] output or null
   int32_t* ids;             // [S, k]
   float* weights;           // [S, k]
-  int32_t* hist;            // [k, E, nb] workspace (nb = 64-token wave blocks)
+  int32_t* hist;            // [nb, k, E] workspace (nb = 64-token wave blocks)
   // the extended gates, for the route kernels that select on final logits
   // themselves (route_fuses_extended): kind 3 is the hierarchical top-k over `groups`
   // groups; temperature > 0 selects on (logits + noise) / temperature
@@ -34,18 +34,12 @@ struct RouteArgs {
   float* part;
 };
 
-struct ScanArgs {
-  int E, k, nb, C;
-  int32_t* hist;     // [k, E, nb]: counts in, exclusive offsets out
-  int32_t* counts;   // [E]
-  int32_t* demand;   // [E] or null
-  int32_t* slot_src; // [E, C]
-};
-
 struct AssignArgs {
   int S, E, k, nb, C;
   const int32_t* ids;  // [S, k]
-  const int32_t* offs; // [k, E, nb]
+  int32_t* hist;       // [nb, k, E] counts; running sums within groups after a large call
+  int32_t* counts;     // [E]
+  int32_t* demand;     // [E] or null
   int32_t* slots;      // [S, k]
   int32_t* slot_src;   // [E, C]
 };
@@ -80,7 +74,7 @@ struct SelectArgs {
                            // unless they are raw itself
   int32_t* ids;            // [S, k]
   float* weights;          // [S, k]
-  int32_t* hist;           // [k, E, nb]
+  int32_t* hist;           // [nb, k, E]
 };
 constexpr int kSelectTileE = 256;  // up to this many experts the block's logits are kept in LDS
 hipError_t launch_select_rows(const SelectArgs& a, hipStream_t st);
@@ -106,11 +100,8 @@ bool route_uses_mfma_rs(const RouteArgs& a);
 bool route_fuses_extended(const RouteArgs& a);
 // True when launch_route can take one K range per block (RouteArgs::part).
 bool route_splits(const RouteArgs& a);
-hipError_t launch_scan(const ScanArgs& a, hipStream_t st);
+// Slots of the capacity rule from the wave blocks' histograms (slots.hip).
 hipError_t launch_assign(const AssignArgs& a, hipStream_t st);
-// Scan and assign, in one launch when the histogram is small (the offsets then
-// stay out of the histogram, which is left as the counts).
-hipError_t launch_scan_assign(const ScanArgs& sa, const AssignArgs& a, hipStream_t st);
 hipError_t launch_dispatch(const RowArgs& a, hipStream_t st);
 hipError_t launch_combine(const RowArgs& a, bool weighted, hipStream_t st);
 hipError_t launch_combine_bwd(const RowArgs& a, hipStream_t st);
@@ -199,7 +190,7 @@ struct BaseArgs {
   float* range_part;       // [3, kBaseRangeBlocks] per-block min, max, NaN/inf flag
   int32_t* ids;            // [S]
   float* weights;          // [S]
-  int32_t* hist;           // [E, nb]
+  int32_t* hist;           // [nb, E]
   double* prices_out;      // [E] or null: final prices
   struct BaseHostFlag* host_flag;  // or null: progress written to host memory for the host's pacing
 };

@@ -177,10 +177,7 @@ __global__ __launch_bounds__(WAVES * 64) void route_mfma_rs_kernel(RouteArgs a) 
       select_token_c<P, KMAX, MODE == 1, SL>(&lg[tt * LGS], a.k, a.normalize, j, valid, a.ids + s * a.k,
                                              a.weights + s * a.k, hist_lds);
     __syncthreads();
-    for (int i = tid; i < a.k * E; i += kThreads) {
-      const int r = i / E, e = i % E;
-      a.hist[(static_cast<int64_t>(r) * E + e) * nb + grp] = hist_lds[i];
-    }
+    for (int i = tid; i < a.k * E; i += kThreads) a.hist[grp * a.k * E + i] = hist_lds[i];
     __syncthreads();  // lg and hist_lds are reused by the next wave block
   };
 

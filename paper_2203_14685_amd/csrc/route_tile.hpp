@@ -68,7 +68,7 @@ __device__ __forceinline__ void tile_epilogue(const RouteArgs& a, float* lg, int
   select_row<P, KMAX, MODE>(lg + t * LGS, E, a.k, a.groups, a.normalize, j, s < a.S, a.ids + s * a.k,
                             a.weights + s * a.k, hist_lds);
   __syncthreads();
-  for (int i = tid; i < a.k * E; i += THREADS) a.hist[static_cast<int64_t>(i) * a.nb + blockIdx.x] = hist_lds[i];
+  for (int i = tid; i < a.k * E; i += THREADS) a.hist[static_cast<int64_t>(blockIdx.x) * a.k * E + i] = hist_lds[i];
 }
 
 // The block's partial sums of one K range into its plane.  put(row, expert, v)

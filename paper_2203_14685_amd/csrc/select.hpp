@@ -407,7 +407,7 @@ __device__ __forceinline__ void select_row(const float* lrow, int E, int k, int 
 }
 
 // ---------------------------------------------------------------- wave-block histogram
-// hist[r][e][wb] = number of tokens of wave block wb whose rank-r choice is e.
+// hist[wb][r][e] = number of tokens of wave block wb whose rank-r choice is e.
 // Every wave of the block calls this (it synchronises the block); `active` waves
 // own a wave block, `s` is the calling lane's token.  The ids are read back from
 // global memory, where the same thread wrote them.
@@ -462,7 +462,7 @@ __device__ __forceinline__ void wave_block_hist(int* lds_w, bool active, int64_t
     __syncthreads();
     if (active)
       for (int i = lane; i < a.E; i += kWave)
-        a.hist[(static_cast<int64_t>(r) * a.E + i) * a.nb + wb] = lds_w[i];
+        a.hist[(static_cast<int64_t>(wb) * a.k + r) * a.E + i] = lds_w[i];
     __syncthreads();
   }
 }

@@ -92,7 +92,7 @@ __global__ __launch_bounds__(kWave * P) void select_rows_kernel(SelectArgs a, in
                             hist_lds);
   __syncthreads();
   for (int i = threadIdx.x; i < a.k * E; i += kThreads)
-    a.hist[static_cast<int64_t>(i) * a.nb + blockIdx.x] = hist_lds[i];
+    a.hist[static_cast<int64_t>(blockIdx.x) * a.k * E + i] = hist_lds[i];
 }
 
 template <int P, int KMAX, int MODE>
