@@ -44,9 +44,11 @@ __device__ __forceinline__ void split_trunc(float v, uint32_t& h, uint32_t& m, u
 }
 __device__ __forceinline__ uint32_t pack_hi(uint32_t a, uint32_t b) { return (a >> 16) | (b & 0xffff0000u); }
 
-// Row stride in LDS (bf16 elements) of rows of 16 n: 32 bytes past a multiple of
-// 128, so that the four rows a transpose read touches lie in different banks.
-constexpr int tr_stride(int n) { return 16 * (n + ((1 - n) & 3)); }
+// Row stride in LDS (bf16 elements) of rows of 16 n: an odd multiple of 32 bytes,
+// and where row t of 32 lies: the 16 rows that one transpose read takes (8 g + 4 h
+// + q for g, q = 0..3) are neighbours, so any 8 of them fill all 64 banks.
+constexpr int tr_stride(int n) { return 16 * (n | 1); }
+__device__ __forceinline__ int tr_row(int t) { return ((t & 4) << 2) | ((t >> 1) & 12) | (t & 3); }
 
 // ---------------------------------------------------------------- dW, bf16
 // Block: CB = 64 WM columns of x times all experts (16 NT, NTW tiles per wave)
@@ -63,7 +65,7 @@ __global__ __launch_bounds__(WM* WN * 64) void dwg_tile_bf16_kernel(GateBwdArgs 
   static_assert(NTW * WN == NT, "whole tiles per wave");
   constexpr int TK = 32;
   constexpr int CB = 64 * WM;
-  constexpr int LDX = CB + 16;  // 2 LDX = 32 mod 128
+  constexpr int LDX = CB + 16;  // an odd multiple of 32 bytes
   constexpr int LDE = tr_stride(NT);
   constexpr int XP = (TK * CB / 8 + THREADS - 1) / THREADS;
   constexpr int LP = (TK * 16 * NT / 4 + THREADS - 1) / THREADS;
@@ -110,7 +112,7 @@ __global__ __launch_bounds__(WM* WN * 64) void dwg_tile_bf16_kernel(GateBwdArgs 
     for (int i = 0; i < XP; ++i) {
       const int p = tid + i * THREADS, t = p / (CB / 8);
       if (XP * THREADS == TK * CB / 8 || t < TK)
-        *reinterpret_cast<u32x4*>(&xs[buf][t * LDX + 8 * (p % (CB / 8))]) = xr[i];
+        *reinterpret_cast<u32x4*>(&xs[buf][tr_row(t) * LDX + 8 * (p % (CB / 8))]) = xr[i];
     }
 #pragma unroll
     for (int i = 0; i < LP; ++i) {
@@ -122,7 +124,7 @@ __global__ __launch_bounds__(WM* WN * 64) void dwg_tile_bf16_kernel(GateBwdArgs 
         split_trunc(__uint_as_float(u), h[q], md[q], lo[q]);
       }
       if (E % 4 == 0) {
-        uint16_t* o = &pl[buf][lrow[i] * LDE + lcol[i]];
+        uint16_t* o = &pl[buf][tr_row(lrow[i]) * LDE + lcol[i]];
         *reinterpret_cast<uint2*>(o) = uint2{pack_hi(h[0], h[1]), pack_hi(h[2], h[3])};
         *reinterpret_cast<uint2*>(o + TK * LDE) = uint2{pack_hi(md[0], md[1]), pack_hi(md[2], md[3])};
         *reinterpret_cast<uint2*>(o + 2 * TK * LDE) = uint2{pack_hi(lo[0], lo[1]), pack_hi(lo[2], lo[3])};
@@ -130,7 +132,7 @@ __global__ __launch_bounds__(WM* WN * 64) void dwg_tile_bf16_kernel(GateBwdArgs 
         int r = lrow[i], c = lcol[i];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          uint16_t* o = &pl[buf][r * LDE + c];
+          uint16_t* o = &pl[buf][tr_row(r) * LDE + c];
           o[0] = static_cast<uint16_t>(h[q] >> 16);
           o[TK * LDE] = static_cast<uint16_t>(md[q] >> 16);
           o[2 * TK * LDE] = static_cast<uint16_t>(lo[q] >> 16);
@@ -162,7 +164,7 @@ __global__ __launch_bounds__(WM* WN * 64) void dwg_tile_bf16_kernel(GateBwdArgs 
       uint2 hf[2];
 #pragma unroll
       for (int h = 0; h < 2; ++h)
-        hf[h] = tr16(&xs[buf][(8 * g + 4 * h + m / 4) * LDX + wm * 64 + 16 * mt + 4 * (m % 4)]);
+        hf[h] = tr16(&xs[buf][(16 * h + 4 * g + m / 4) * LDX + wm * 64 + 16 * mt + 4 * (m % 4)]);
       av[mt] = u32x4{hf[0].x, hf[0].y, hf[1].x, hf[1].y};
     }
 #pragma unroll
@@ -172,7 +174,7 @@ __global__ __launch_bounds__(WM* WN * 64) void dwg_tile_bf16_kernel(GateBwdArgs 
         uint2 hf[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
-          hf[h] = tr16(&pl[buf][(p * TK + 8 * g + 4 * h + m / 4) * LDE + (wn * NTW + nt) * 16 + 4 * (m % 4)]);
+          hf[h] = tr16(&pl[buf][(p * TK + 16 * h + 4 * g + m / 4) * LDE + (wn * NTW + nt) * 16 + 4 * (m % 4)]);
         const u32x4 bv = {hf[0].x, hf[0].y, hf[1].x, hf[1].y};
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) acc[mt][nt] = mfma_b16(av[mt], bv, acc[mt][nt]);

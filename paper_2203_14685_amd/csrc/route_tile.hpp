@@ -24,6 +24,11 @@ __device__ __forceinline__ uint2 lds_tr16(const uint16_t* p) {
   return __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p)));
 }
 
+// Where row k of 32 (a K step) lies in LDS: rows 8 g + 4 h + q, which one transpose
+// read takes for g = 0..3 and q = 0..3, are 16 neighbours.  With a row stride of an
+// odd multiple of 32 bytes any 8 neighbours' 32-byte pieces fill all 64 banks.
+__device__ __forceinline__ int tr_row(int k) { return (k & ~31) | ((k & 4) << 2) | ((k >> 1) & 12) | (k & 3); }
+
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rsrc(const void* p, unsigned bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, static_cast<int>(bytes), 0x00020000);
 }

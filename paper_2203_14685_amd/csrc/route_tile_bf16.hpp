@@ -80,9 +80,8 @@ __global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs 
 #pragma unroll
     for (int i = 0; i < WP; ++i) {
       if (tid + i * THREADS >= wcnt) continue;
-      uint16_t* dst = &ws[wrow[i] * LDW + wcol[i]];
       if (E % 8 == 0) {
-        *reinterpret_cast<u32x4*>(dst) = wr[i];
+        *reinterpret_cast<u32x4*>(&ws[tr_row(wrow[i]) * LDW + wcol[i]]) = wr[i];
       } else {
         // the piece crosses rows of W: element pairs where E is even, single
         // elements where it is odd
@@ -90,14 +89,14 @@ __global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs 
         if (E % 2 == 0) {
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            *reinterpret_cast<uint32_t*>(&ws[r * LDW + c]) = wr[i][q];
+            *reinterpret_cast<uint32_t*>(&ws[tr_row(r) * LDW + c]) = wr[i][q];
             c += 2;
             if (c >= E) { c = 0; ++r; }
           }
         } else {
 #pragma unroll
           for (int q = 0; q < 8; ++q) {
-            ws[r * LDW + c] = static_cast<uint16_t>(wr[i][q / 2] >> (16 * (q & 1)));
+            ws[tr_row(r) * LDW + c] = static_cast<uint16_t>(wr[i][q / 2] >> (16 * (q & 1)));
             c += 1;
             if (c >= E) { c = 0; ++r; }
           }
@@ -128,7 +127,7 @@ __global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs 
         uint2 half[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h)
-          half[h] = lds_tr16(&ws[(32 * ks + 8 * g + 4 * h + m / 4) * LDW + (wn * NTW + nt) * 16 + 4 * (m % 4)]);
+          half[h] = lds_tr16(&ws[(32 * ks + 16 * h + 4 * g + m / 4) * LDW + (wn * NTW + nt) * 16 + 4 * (m % 4)]);
         const u32x4 bv = {half[0].x, half[0].y, half[1].x, half[1].y};
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
