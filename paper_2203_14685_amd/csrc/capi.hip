@@ -205,9 +205,8 @@ GateBwdPlan plan_gate_bwd(const moe_gate_bwd_params* p) {
   // blocks of 256 columns, two per CU, or 1024 vector blocks of 64), each range
   // a whole number of 64-token blocks; matrix-core ranges keep at least 4 of
   // them where the batch allows, so that each block pipelines several chunks
-  // tiled bf16 shapes: one block of 128 columns and 8 waves per CU past 128
-  // experts (8192 x 4096, E = 256: 118 us at 128 blocks, see the kernel at 256),
-  // else of 256 columns
+  // tiled bf16 shapes: one block of 128 columns per CU past 128 experts (8192 x
+  // 4096, E = 256: 118 us at 128 blocks, 76 us at 256), else of 256 columns
   const bool tiled = !g.mfma && p->dtype == MOE_BF16 && gate_bwd_tile_shape(p->E, p->d);
   const int64_t per_split = g.mfma ? (p->d + 255) / 256
                             : tiled ? (p->d + (p->E > 128 ? 127 : 255)) / (p->E > 128 ? 128 : 256)
@@ -357,7 +356,7 @@ moe_status moe_gate_bwd(const moe_gate_bwd_params* p, const void* x, const void*
   a.tile_dx = (dx && !a.mfma_dx && gate_bwd_tile_shape(p->E, p->d) && aligned(wg, 16)) ? 1 : 0;
   a.s_pad = g.s_pad;
   // with dW wanted, its reduction launch also takes db and the balance loss
-  a.sums_in_reduce = (dwg && p->E <= 64) ? 1 : 0;
+  a.sums_in_reduce = (dwg && p->E <= 256) ? 1 : 0;
   a.x = x; a.wg = wg; a.logits = logits; a.ids = ids; a.dw = dw;
   a.dl = dlogits ? dlogits : reinterpret_cast<float*>(ws + g.off_dl);
   a.dlt = a.mfma_dw ? reinterpret_cast<uint16_t*>(ws + g.off_dlt) : nullptr;

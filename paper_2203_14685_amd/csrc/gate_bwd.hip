@@ -435,25 +435,27 @@ __global__ __launch_bounds__(1024) void aux_loss_kernel(GateBwdArgs a) {
   if (t == 0) a.aux_loss[0] = a.aux_coef * static_cast<float>(a.E) * red[0];
 }
 
-// db and the balance loss side by side (E <= 64), block sb of 1024 threads:
-// with dbias, block 0 sums the per-wave-block dL sums into it; the other sums
-// the softmax sums into pe and then forms the loss from them (first-choice
-// counts), so no block waits for another.
+// db and the balance loss side by side (E <= 256), block sb of 1024 threads: with
+// dbias, block 0 sums the per-wave-block dL sums into it; the other sums the
+// softmax sums into pe and then forms the loss from them (first-choice counts), so
+// no block waits for another.
+constexpr int kSumsMaxE = 256;
+
 __device__ __forceinline__ void dl_sums_block(const GateBwdArgs& a, int sb, float (*red)[kWave]) {
-  if (a.dbias && sb == 0) {
-    colsum_cols(a.bpart, a.nb, a.E, a.dbias, 0, red);
-    return;
+  const bool db = a.dbias && sb == 0;
+  float loss = 0.f;
+  for (int cb = 0; cb * kWave < a.E; ++cb) {
+    if (cb > 0) __syncthreads();  // red is reused
+    const float pe = colsum_cols(db ? a.bpart : a.ppart, a.nb, a.E, db ? a.dbias : a.pe, cb, red);
+    const int e = cb * kWave + static_cast<int>(threadIdx.x);
+    if (!db && threadIdx.x < kWave && e < a.E && a.S > 0) {  // the loss is the first wave's
+      const float inv_s = 1.f / static_cast<float>(a.S);
+      loss += (static_cast<float>(first_count(a, e)) * inv_s) * (pe * inv_s);
+    }
   }
-  const float pe = colsum_cols(a.ppart, a.nb, a.E, a.pe, 0, red);
-  if (threadIdx.x >= kWave) return;  // the loss is the first wave's (a whole wave)
-  const int e = threadIdx.x;
-  float term = 0.f;
-  if (e < a.E && a.S > 0) {
-    const float inv_s = 1.f / static_cast<float>(a.S);
-    term = (static_cast<float>(first_count(a, e)) * inv_s) * (pe * inv_s);
-  }
-  term = wave_sum(term);
-  if (e == 0) a.aux_loss[0] = a.aux_coef * static_cast<float>(a.E) * term;
+  if (db || threadIdx.x >= kWave) return;
+  loss = wave_sum(loss);
+  if (threadIdx.x == 0) a.aux_loss[0] = a.aux_coef * static_cast<float>(a.E) * loss;
 }
 
 // Blocks of the sums above: db if wanted, the loss if wanted.
@@ -872,32 +874,40 @@ __global__ __launch_bounds__(kBwdThreads) void dwg_partial_kernel(GateBwdArgs a)
 }
 
 // dwg[j][e] = sum over the token ranges, in order; blocks past the sums run
-// the db / balance-loss sums (sums_in_reduce).
+// the db / balance-loss sums (sums_in_reduce).  A block takes 32 columns of 32
+// experts: it reads the ranges along the columns and, through LDS, writes along
+// the experts, so both sides are whole 128-byte lines (a thread per output wrote 4
+// bytes per line: 8 ranges of 4096 x 256 took 10.1 us).
 constexpr int kReduceThreads = 1024;
 
-__global__ __launch_bounds__(kReduceThreads) void dwg_reduce_kernel(GateBwdArgs a) {
-  const int64_t n = static_cast<int64_t>(a.E) * a.d;
-  const int64_t nr = (n + kReduceThreads - 1) / kReduceThreads;
-  if (static_cast<int64_t>(blockIdx.x) >= nr) {
+__global__ __launch_bounds__(kReduceThreads) void dwg_reduce_kernel(GateBwdArgs a, int nr) {
+  if (static_cast<int>(blockIdx.x) >= nr) {
     __shared__ float red[16][kWave];
-    dl_sums_block(a, static_cast<int>(blockIdx.x - nr), red);
+    dl_sums_block(a, static_cast<int>(blockIdx.x) - nr, red);
     return;
   }
-  const int64_t idx = static_cast<int64_t>(blockIdx.x) * kReduceThreads + threadIdx.x;
-  if (idx >= n) return;
-  const int e = static_cast<int>(idx / a.d), jx = static_cast<int>(idx % a.d);
-  // eight ranges' loads in flight at a time; the additions stay in range order
-  float v = 0.f;
-  int sp = 0;
-  for (; sp + 8 <= a.nsplit; sp += 8) {
-    float t[8];
+  __shared__ float tile[32][33];
+  const int64_t n = static_cast<int64_t>(a.E) * a.d;
+  const int ncb = (a.d + 31) / 32;
+  const int j0 = (blockIdx.x % ncb) * 32, e0 = (blockIdx.x / ncb) * 32;
+  const int r = threadIdx.x / 32, c = threadIdx.x % 32;
+  if (e0 + r < a.E && j0 + c < a.d) {
+    const float* p = a.wpart + static_cast<int64_t>(e0 + r) * a.d + j0 + c;
+    // eight ranges' loads in flight at a time; the additions stay in range order
+    float v = 0.f;
+    int sp = 0;
+    for (; sp + 8 <= a.nsplit; sp += 8) {
+      float t[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) t[u] = a.wpart[static_cast<int64_t>(sp + u) * n + idx];
+      for (int u = 0; u < 8; ++u) t[u] = p[static_cast<int64_t>(sp + u) * n];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v += t[u];
+      for (int u = 0; u < 8; ++u) v += t[u];
+    }
+    for (; sp < a.nsplit; ++sp) v += p[static_cast<int64_t>(sp) * n];
+    tile[r][c] = v;
   }
-  for (; sp < a.nsplit; ++sp) v += a.wpart[static_cast<int64_t>(sp) * n + idx];
-  a.dwg[static_cast<int64_t>(jx) * a.E + e] = v;
+  __syncthreads();
+  if (e0 + c < a.E && j0 + r < a.d) a.dwg[static_cast<int64_t>(j0 + r) * a.E + e0 + c] = tile[c][r];
 }
 
 // Block: 64 tokens x 64 columns.  Thread (column jj, token group tg) keeps the
@@ -957,10 +967,11 @@ __global__ __launch_bounds__(kBwdThreads) void dx_kernel(GateBwdArgs a) {
 // ---------------------------------------------------------------- launchers
 template <int P, int EPL>
 static void launch_dl_t(const GateBwdArgs& a, hipStream_t st) {
-  // up to 16 waves per 64-token block (one pass each up to 128 experts, four up
-  // to 256: 16 passes of 4 waves took 49 us at 8192 tokens) while the sums fit LDS
+  // up to 16 waves per 64-token block, one pass each, while the sums fit LDS; 8
+  // waves of 4 passes past 128 experts, whose lists take more registers (8192 x
+  // 256: 4 waves of 64 lanes per token 49 us, 16 26.4, 8 of 32 lanes 25.2)
   constexpr int TP = kWave / P;
-  constexpr int WAVES = P <= 32 ? (kWave / TP < 16 ? kWave / TP : 16) : EPL <= 4 ? 16 : 4;
+  constexpr int WAVES = P <= 32 ? (kWave / TP < 16 ? kWave / TP : EPL > 4 ? 8 : 16) : 4;
   const size_t tile = a.dlt ? static_cast<size_t>(kWave) * (a.E + 1) * sizeof(float) : 0;
   const size_t sums = static_cast<size_t>(2 * WAVES) * a.E * sizeof(float);
   const int rows = count_rows(a.S);
@@ -993,12 +1004,12 @@ hipError_t launch_gate_bwd_dl(const GateBwdArgs& a, hipStream_t st) {
     else if (E <= 32) launch_dl_t<8, 4>(a, st);
     else if (E <= 64) launch_dl_t<16, 4>(a, st);
     else if (E <= 128) launch_dl_t<32, 4>(a, st);
-    else if (E <= 256) launch_dl_t<64, 4>(a, st);
+    else if (E <= 256) launch_dl_t<32, 8>(a, st);
     else if (E <= 512) launch_dl_t<64, 8>(a, st);
     else launch_dl_t<64, 16>(a, st);
   }
   if (a.sums_in_reduce) return hipGetLastError();  // the dW reduction launch takes them
-  if (a.E <= kWave && dl_sums_blocks(a) > 0) {
+  if (a.E <= kSumsMaxE && dl_sums_blocks(a) > 0) {
     // db and the loss in one launch
     dl_sums_loss_kernel<<<dim3(dl_sums_blocks(a)), dim3(1024), 0, st>>>(a);
     return hipGetLastError();
@@ -1042,10 +1053,9 @@ hipError_t launch_gate_bwd_dwg(const GateBwdArgs& a, hipStream_t st) {
       else dwg_partial_kernel<float, kDwEC><<<grid, dim3(kBwdThreads), 0, st>>>(a);
     }
   }
-  const int64_t n = static_cast<int64_t>(a.E) * a.d;
-  const int64_t nr = (n + kReduceThreads - 1) / kReduceThreads;
+  const int64_t nr = static_cast<int64_t>((a.d + 31) / 32) * ((a.E + 31) / 32);
   const int64_t extra = a.sums_in_reduce ? dl_sums_blocks(a) : 0;
-  dwg_reduce_kernel<<<dim3(static_cast<unsigned>(nr + extra)), dim3(kReduceThreads), 0, st>>>(a);
+  dwg_reduce_kernel<<<dim3(static_cast<unsigned>(nr + extra)), dim3(kReduceThreads), 0, st>>>(a, static_cast<int>(nr));
   return hipGetLastError();
 }
 

@@ -21,6 +21,10 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_of(const void* p, unsigne
 __device__ __forceinline__ u32x4 load16(__amdgpu_buffer_rsrc_t r, int off) {
   return __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
 }
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u32x2 load8(__amdgpu_buffer_rsrc_t r, int off) {
+  return __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+}
 __device__ __forceinline__ uint32_t load4(__amdgpu_buffer_rsrc_t r, int off) {
   return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
 }
@@ -58,6 +62,9 @@ __device__ __forceinline__ int tr_row(int t) { return ((t & 4) << 2) | ((t >> 1)
 // bf16 planes in the same order, so no transposed copy of dL is needed from the
 // kernel before and the workspace stays what the vector path asks for.  Both
 // operands are transpose reads.  64 tokens are summed on their own, then added.
+// Bound by its stages (8192 x 4096, E = 256: 67 us; without the staging 47, without
+// the products 47, with neither and no reads 18): waves of 64 columns x 32 experts,
+// four per SIMD, overlap them better than half as many of 64 x 64 (73 us).
 template <int NT, int WM, int WN>
 __global__ __launch_bounds__(WM* WN * 64) void dwg_tile_bf16_kernel(GateBwdArgs a) {
   constexpr int THREADS = WM * WN * kWave;
@@ -149,15 +156,20 @@ __global__ __launch_bounds__(WM* WN * 64) void dwg_tile_bf16_kernel(GateBwdArgs 
 #pragma unroll
     for (int nt = 0; nt < NTW; ++nt) sum[mt][nt] = acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+  // of the two waves that a SIMD holds of an eight-wave block, one stages before it
+  // multiplies and one after: one's conversions meet the other's products
+  const bool early = (__builtin_amdgcn_readfirstlane(w) & 4) == 0;
   load(sb);
   stage(0);
   load(sb + TK);
   __syncthreads();
   int buf = 0;
   for (int64_t s0 = sb; s0 < se; s0 += TK) {
-    stage(buf ^ 1);  // zeros after the last
-    load(s0 + 2 * TK);
-    __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the products
+    if (early) {
+      stage(buf ^ 1);  // zeros after the last
+      load(s0 + 2 * TK);
+      __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the products
+    }
     u32x4 av[4];
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) {
@@ -187,6 +199,10 @@ __global__ __launch_bounds__(WM* WN * 64) void dwg_tile_bf16_kernel(GateBwdArgs 
           sum[mt][nt] += acc[mt][nt];
           acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
+    }
+    if (!early) {
+      stage(buf ^ 1);
+      load(s0 + 2 * TK);
     }
     __syncthreads();
     buf ^= 1;
@@ -322,13 +338,18 @@ __global__ __launch_bounds__(kDxThreads) void dx_tile_bf16_kernel(GateBwdArgs a,
   const int pcol = 32 * (m >> 3) + 16 * (g & 1) + 8 * (g >> 1);
   const bool lo8 = m < 8;
   uint16_t* dx = reinterpret_cast<uint16_t*>(a.dx);
-  for (int cb = 0; cb < passes; ++cb) {
-    const int j0 = jb + cb * 64;
-    if (j0 >= d) break;  // the same for the whole block
-    const uint16_t* ws = wl[cb & 1];
-    stage_w(wl[cb & 1]);
-    __syncthreads();
-    load_w(cb + 1 < passes ? j0 + 64 : d);
+  const bool early = (__builtin_amdgcn_readfirstlane(w) & 4) == 0;
+  const int jend = min(jb + CB, d);
+  stage_w(wl[0]);
+  load_w(jb + 64 < jend ? jb + 64 : d);
+  __syncthreads();
+  int buf = 0;
+  for (int j0 = jb; j0 < jend; j0 += 64) {
+    const uint16_t* ws = wl[buf];
+    if (early) {
+      stage_w(wl[buf ^ 1]);
+      load_w(j0 + 128 < jend ? j0 + 128 : d);
+    }
     const int j = j0 + pcol;
     u32x4 din[2] = {zero, zero};
     if constexpr (ACC) {
@@ -386,6 +407,12 @@ __global__ __launch_bounds__(kDxThreads) void dx_tile_bf16_kernel(GateBwdArgs a,
                                           pack_bf16x2(o[6], o[7])},
                                     reinterpret_cast<u32x4*>(dx + s * d + j));
     }
+    if (!early) {
+      stage_w(wl[buf ^ 1]);
+      load_w(j0 + 128 < jend ? j0 + 128 : d);
+    }
+    __syncthreads();
+    buf ^= 1;
   }
 }
 
@@ -398,28 +425,33 @@ __device__ __forceinline__ int dl_expert(int nt, int n) {
   else return n * NT + nt;
 }
 
-// Block: 4 waves of 64 columns times 16 NT experts (blockIdx.y: which) over one
-// token range, in stages of 32 tokens.  x goes from memory to registers: a lane
-// loads 4 adjacent columns of token 4 t + g, and column 4 m + mt is row m of tile
-// mt.  dL's rows are staged in LDS, double buffered.  Each 64 tokens are summed
-// on their own, then added.
-template <int NT>
-__global__ __launch_bounds__(256) void dwg_tile_f32_kernel(GateBwdArgs a) {
-  constexpr int TK = 32, XQ = TK / 4;
+// Block: 2 x 4 waves of 16 MT columns times 16 NT experts (blockIdx.y: which) over one
+// token range, in stages of 64 tokens, each half of the waves 32 of them.  x goes
+// from memory to registers: a lane loads MT adjacent columns of token 4 t + g, and
+// column MT m + mt is row m of tile mt.  dL's rows are staged in LDS, double
+// buffered.  A half sums 64 tokens (two stages) on their own, then adds them; the
+// halves meet in LDS.
+template <int NT, int MT>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(MT == 2 ? 4 : 1))) void dwg_tile_f32_kernel(GateBwdArgs a) {
+  constexpr int TH = 32, TK = 2 * TH, XQ = TH / 4;
   constexpr int EB = 16 * NT;
-  constexpr int LP = TK * EB / 256;  // single values per thread: rows of EB out of E
-  __shared__ __align__(16) float ds[2][TK * EB];
+  constexpr int LP = TK * EB / 512;  // single values per thread: rows of EB out of E
+  constexpr int kStage = 2 * TK * EB, kHalf = 4 * 16 * MT * EB;
+  __shared__ __align__(16) float ds[kStage > kHalf ? kStage : kHalf];
   const int tid = threadIdx.x;
   const int w = tid / kWave, lane = lane_id(), g = lane / 16, m = lane % 16;
+  const int hs = w / 4, wc = w % 4;
   const int d = a.d, E = a.E;
-  const int ncb = (d + 255) / 256;
+  constexpr int CW = 16 * MT, CB = 4 * CW;  // columns per wave and block
+  const int ncb = (d + CB - 1) / CB;
   const int split = blockIdx.x / ncb;
-  const int j = (blockIdx.x % ncb) * 256 + w * 64 + 4 * m;
+  const int jw = (blockIdx.x % ncb) * CB + wc * CW;
+  const int j = jw + MT * m;
   const int e0 = blockIdx.y * EB;
   const int64_t sb = static_cast<int64_t>(split) * a.split_tokens;
   const int64_t se = min(static_cast<int64_t>(a.S), sb + a.split_tokens);
 
-  u32x4 xr[XQ], xn[XQ];
+  uint32_t xr[XQ][MT], xn[XQ][MT];
   uint32_t lr[LP];
   auto load = [&](int64_t s0) {
     const int rows = static_cast<int>(max(min(static_cast<int64_t>(TK), se - s0), static_cast<int64_t>(0)));
@@ -428,34 +460,52 @@ __global__ __launch_bounds__(256) void dwg_tile_f32_kernel(GateBwdArgs a) {
         rsrc_of(reinterpret_cast<const float*>(a.x) + sx * d, static_cast<unsigned>(rows) * d * 4u);
     const __amdgpu_buffer_rsrc_t lsrc = rsrc_of(a.dl + sx * E, static_cast<unsigned>(rows) * E * 4u);
 #pragma unroll
-    for (int q = 0; q < XQ; ++q) xn[q] = load16(xsrc, j < d ? ((4 * q + g) * d + j) * 4 : kOob);
+    for (int q = 0; q < XQ; ++q) {
+      const int o = j < d ? ((hs * TH + 4 * q + g) * d + j) * 4 : kOob;
+      if constexpr (MT == 4) {
+        const u32x4 v = load16(xsrc, o);
+        xn[q][0] = v.x; xn[q][1] = v.y; xn[q][2] = v.z; xn[q][3] = v.w;
+      } else {
+        const u32x2 v = load8(xsrc, o);
+        xn[q][0] = v.x; xn[q][1] = v.y;
+      }
+    }
 #pragma unroll
     for (int i = 0; i < LP; ++i) {
-      const int p = tid + i * 256, t = p / EB, e = e0 + p % EB;
+      const int p = tid + i * 512, t = p / EB, e = e0 + p % EB;
       lr[i] = load4(lsrc, e < E ? (t * E + e) * 4 : kOob);
     }
   };
-  auto stage = [&](int buf) {
+  f32x4 sum[MT][NT], acc[MT][NT];
 #pragma unroll
-    for (int i = 0; i < LP; ++i) ds[buf][tid + i * 256] = __uint_as_float(lr[i]);
-#pragma unroll
-    for (int q = 0; q < XQ; ++q) xr[q] = xn[q];
-  };
-  f32x4 sum[4][NT], acc[4][NT];
-#pragma unroll
-  for (int mt = 0; mt < 4; ++mt)
+  for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) sum[mt][nt] = acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto flush = [&]() {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        sum[mt][nt] += acc[mt][nt];
+        acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+  };
   load(sb);
   int buf = 0;
   for (int64_t s0 = sb; s0 < se; s0 += TK) {
-    stage(buf);  // last read two stages ago, before the previous barrier
+    // the buffer was last read two stages ago, before the previous barrier
+#pragma unroll
+    for (int i = 0; i < LP; ++i) ds[buf * TK * EB + tid + i * 512] = __uint_as_float(lr[i]);
+#pragma unroll
+    for (int q = 0; q < XQ; ++q)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) xr[q][mt] = xn[q][mt];
     __syncthreads();
     load(s0 + TK);
     __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the products
 #pragma unroll
     for (int q = 0; q < XQ; ++q) {
-      const float* row = &ds[buf][(4 * q + g) * EB];
+      const float* row = &ds[(buf * TK + hs * TH + 4 * q + g) * EB];
       float b[NT];
       if constexpr (NT % 4 == 0) {
 #pragma unroll
@@ -470,27 +520,33 @@ __global__ __launch_bounds__(256) void dwg_tile_f32_kernel(GateBwdArgs a) {
         b[0] = row[m];
       }
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
+      for (int mt = 0; mt < MT; ++mt) {
         const uint32_t xu = xr[q][mt];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
           acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(xu), b[nt], acc[mt][nt], 0, 0, 0);
       }
     }
-    if (buf) {
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-          sum[mt][nt] += acc[mt][nt];
-          acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-        }
-    }
+    if (buf) flush();
     buf ^= 1;
   }
-  // lane (g, m) of tile (mt, nt): columns 4 (4 g + i) + mt, so its 4 tiles hold 4
+  flush();
+  __syncthreads();  // the stages are consumed
+  f32x4* half = reinterpret_cast<f32x4*>(ds);  // [4 waves][MT NT][64 lanes]
+  if (hs == 1) {
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) half[(wc * MT * NT + mt * NT + nt) * kWave + lane] = sum[mt][nt];
+  }
+  __syncthreads();
+  if (hs == 1) return;
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) sum[mt][nt] += half[(wc * MT * NT + mt * NT + nt) * kWave + lane];
+  // lane (g, m) of tile (mt, nt): columns MT (4 g + i) + mt, so its tiles hold MT
   // adjacent columns for each i
-  const int jw = (blockIdx.x % ncb) * 256 + w * 64;
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
     const int e = e0 + dl_expert<NT>(nt, m);
@@ -498,11 +554,12 @@ __global__ __launch_bounds__(256) void dwg_tile_f32_kernel(GateBwdArgs a) {
     float* o = a.wpart + (static_cast<int64_t>(split) * E + e) * d;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int c = jw + 4 * (4 * g + i);
-      if (c < d)
-        *reinterpret_cast<f32x4*>(o + c) =
-            f32x4{sum[0][nt][i] + acc[0][nt][i], sum[1][nt][i] + acc[1][nt][i], sum[2][nt][i] + acc[2][nt][i],
-                  sum[3][nt][i] + acc[3][nt][i]};
+      const int c = jw + MT * (4 * g + i);
+      if (c >= d) continue;
+      if constexpr (MT == 4)
+        *reinterpret_cast<f32x4*>(o + c) = f32x4{sum[0][nt][i], sum[1][nt][i], sum[2][nt][i], sum[3][nt][i]};
+      else
+        *reinterpret_cast<float2*>(o + c) = float2{sum[0][nt][i], sum[1][nt][i]};
     }
   }
 }
@@ -582,13 +639,18 @@ __global__ __launch_bounds__(kDxThreads) void dx_tile_f32_kernel(GateBwdArgs a, 
   }
   float* dx = reinterpret_cast<float*>(a.dx);
   const int arow = 8 * (m / 4) + m % 4;  // column of A row m in tile 0 of a pair; tile 1 is 4 on
+  const bool early = (__builtin_amdgcn_readfirstlane(w) & 4) == 0;
   int buf = 0;
   const int jend = min(jb + CB, d);
+  stage_w(wl[0]);
+  load_w(jb + PC < jend ? jb + PC : d);
+  __syncthreads();
   for (int j0 = jb; j0 < jend; j0 += PC) {
     const float* ws = wl[buf];
-    stage_w(wl[buf]);
-    __syncthreads();
-    load_w(j0 + PC < jend ? j0 + PC : d);
+    if (early) {
+      stage_w(wl[buf ^ 1]);
+      load_w(j0 + 2 * PC < jend ? j0 + 2 * PC : d);
+    }
 #pragma unroll
     for (int pr = 0; pr < PC / 32; ++pr) {
       const int j = j0 + 32 * pr + 8 * g;
@@ -618,6 +680,11 @@ __global__ __launch_bounds__(kDxThreads) void dx_tile_f32_kernel(GateBwdArgs a, 
       if (ok) *reinterpret_cast<f32x4*>(o) = acc[0] + in[0];
       if (ok1) *reinterpret_cast<f32x4*>(o + 4) = acc[1] + in[1];
     }
+    if (!early) {
+      stage_w(wl[buf ^ 1]);
+      load_w(j0 + 2 * PC < jend ? j0 + 2 * PC : d);
+    }
+    __syncthreads();
     buf ^= 1;
   }
 }
@@ -629,25 +696,26 @@ static void launch_dwg_b16(const GateBwdArgs& a, hipStream_t st) {
   dwg_tile_bf16_kernel<NT, WM, WN><<<dim3(static_cast<unsigned>(blocks)), dim3(WM * WN * kWave), 0, st>>>(a);
 }
 
-template <int NT>
+template <int NT, int MT>
 static void launch_dwg_f32(const GateBwdArgs& a, hipStream_t st) {
-  const int64_t blocks = static_cast<int64_t>((a.d + 255) / 256) * a.nsplit;
-  dwg_tile_f32_kernel<NT><<<dim3(static_cast<unsigned>(blocks), (a.E + 16 * NT - 1) / (16 * NT)), dim3(256), 0, st>>>(a);
+  const int64_t blocks = static_cast<int64_t>((a.d + 64 * MT - 1) / (64 * MT)) * a.nsplit;
+  dwg_tile_f32_kernel<NT, MT>
+      <<<dim3(static_cast<unsigned>(blocks), (a.E + 16 * NT - 1) / (16 * NT)), dim3(512), 0, st>>>(a);
 }
 
 void launch_dwg_tile(const GateBwdArgs& a, hipStream_t st) {
   if (a.dtype == 1) {
     if (a.E <= 16) launch_dwg_b16<1, 4, 1>(a, st);
     else if (a.E <= 32) launch_dwg_b16<2, 4, 1>(a, st);
-    else if (a.E <= 64) launch_dwg_b16<4, 4, 1>(a, st);
-    else if (a.E <= 128) launch_dwg_b16<8, 4, 2>(a, st);
-    else if (a.E <= 192) launch_dwg_b16<12, 2, 3>(a, st);
-    else launch_dwg_b16<16, 2, 4>(a, st);
+    else if (a.E <= 64) launch_dwg_b16<4, 4, 2>(a, st);
+    else if (a.E <= 128) launch_dwg_b16<8, 4, 4>(a, st);
+    else if (a.E <= 192) launch_dwg_b16<12, 2, 6>(a, st);
+    else launch_dwg_b16<16, 2, 8>(a, st);
     return;
   }
-  if (a.E <= 16) launch_dwg_f32<1>(a, st);
-  else if (a.E <= 32) launch_dwg_f32<2>(a, st);
-  else launch_dwg_f32<4>(a, st);
+  if (a.E <= 16) launch_dwg_f32<1, 4>(a, st);
+  else if (a.E <= 32) launch_dwg_f32<2, 4>(a, st);
+  else launch_dwg_f32<4, 2>(a, st);
 }
 
 // Passes per dx block of PC columns: as few as give `target` blocks, so that a
@@ -662,7 +730,7 @@ static int dx_passes(const GateBwdArgs& a, int PC, int64_t tb, int target) {
 
 template <int KS>
 static void launch_dx_b16(const GateBwdArgs& a, int64_t tb, hipStream_t st) {
-  const int passes = dx_passes(a, 64, tb, 512);
+  const int passes = dx_passes(a, 64, tb, KS > 4 ? 256 : 512);
   const dim3 grid(static_cast<unsigned>(tb * ((a.d + 64 * passes - 1) / (64 * passes)))), block(kDxThreads);
   if (a.accumulate) dx_tile_bf16_kernel<KS, true><<<grid, block, 0, st>>>(a, passes);
   else dx_tile_bf16_kernel<KS, false><<<grid, block, 0, st>>>(a, passes);

@@ -145,6 +145,10 @@ __global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs 
   // is multiplied; one barrier per stage.  A range's sums start from zero and
   // ranges are added in order, so a block that takes all of them gives the same
   // logits as blocks that take one each.
+  // Of the two waves that a SIMD holds of an eight-wave block, one stages before it
+  // multiplies and one after, so that one's LDS writes meet the other's products
+  // (all waves are at the same stage).
+  const bool early = __builtin_amdgcn_readfirstlane(w) < 4;
   const int z0 = MODE == kTilePart ? blockIdx.y : 0;
   const int z1 = MODE == kTilePart ? z0 + 1 : a.zsplit;
   for (int z = z0; z < z1; ++z) {
@@ -162,10 +166,16 @@ __global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs 
 #pragma unroll
       for (int q = 1; q <= DEPTH; ++q) {
         const int set = q % DEPTH;
-        stage(xq[set], wq[set], buf ^ 1);
-        load(xq[set], wq[set], kc + (DEPTH + 1) * KC, kend);
-        __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the products
+        if (early) {
+          stage(xq[set], wq[set], buf ^ 1);
+          load(xq[set], wq[set], kc + (DEPTH + 1) * KC, kend);
+          __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the products
+        }
         multiply(buf);
+        if (!early) {
+          stage(xq[set], wq[set], buf ^ 1);
+          load(xq[set], wq[set], kc + (DEPTH + 1) * KC, kend);
+        }
         __syncthreads();
         buf ^= 1;
         kc += KC;
