@@ -348,9 +348,30 @@ __device__ __forceinline__ void pop_all(KeyList<KMAX>& list, int (&key)[KMAX], i
   if constexpr (R + 1 < KMAX) pop_all<P, KMAX, R + 1>(list, key, id);
 }
 
+// Choice r of the first k is written by lane r % P, which also counts it.
+template <int P, int KMAX>
+__device__ __forceinline__ void write_choices(const int (&key)[KMAX], const int (&id)[KMAX], float top, float inv, int k,
+                                              int E, int j, bool valid, int32_t* ids, float* weights, int* hist_lds) {
+#pragma unroll
+  for (int r = 0; r < KMAX; ++r) {
+    if (r < k && valid && j == r % P) {
+      ids[r] = id[r];
+      weights[r] = (r == 0 ? 1.f : __expf(key_logit(key[r]) - top)) * inv;
+      atomicAdd(&hist_lds[r * E + id[r]], 1);
+    }
+  }
+}
+
+// 1 / t where that is exact (t a power of two with a normal reciprocal), so that
+// x * (1 / t) is x / t rounded once, else 0.
+__device__ __forceinline__ float exact_reciprocal(float t) {
+  const uint32_t u = __float_as_uint(t);
+  const uint32_t exp = u >> 23;
+  return (u & 0x007fffffu) == 0 && exp >= 1 && exp <= 252 ? __uint_as_float((254 - exp) << 23) : 0.f;
+}
+
 // MODE: 0 top-k, 1 kTop1, 3 hierarchical top-k.  All P lanes call this
-// together.  Choice r is written by lane r % P, which also counts it in
-// hist_lds[r][id].
+// together.
 template <int P, int KMAX, int MODE>
 __device__ __forceinline__ void select_row(const float* lrow, int E, int k, int groups, int normalize, int j,
                                            bool valid, int32_t* ids, float* weights, int* hist_lds) {
@@ -394,15 +415,7 @@ __device__ __forceinline__ void select_row(const float* lrow, int E, int k, int 
     } else {
       z = row_expsum<P>(lrow, 0, E, j, top);
     }
-    const float inv = 1.f / z;
-#pragma unroll
-    for (int r = 0; r < KMAX; ++r) {
-      if (r < k && valid && j == r % P) {
-        ids[r] = id[r];
-        weights[r] = (r == 0 ? 1.f : __expf(key_logit(key[r]) - top)) * inv;
-        atomicAdd(&hist_lds[r * E + id[r]], 1);
-      }
-    }
+    write_choices<P, KMAX>(key, id, top, 1.f / z, k, E, j, valid, ids, weights, hist_lds);
   }
 }
 
