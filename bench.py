@@ -54,7 +54,7 @@ def kernel_of_op(op, w):
     slot = (lambda t, sc, d: f"slot_rows_pow2_kernel<{t}, {sc}, {d}, {lg}") if fast else \
         (lambda t, sc, d: f"slot_rows_kernel<{t}, {sc}, {d}, {p2}")
     if k > 1:
-        cbwd = f"combine_bwd_scatter_kernel<{elt}, {'true' if dw else 'false'}>"
+        cbwd = f"combine_bwd_scatter_kernel<{elt}, {'true' if dw else 'false'},"
     elif dw and not (pow2 and 64 <= nch <= 512):
         cbwd = f"combine_bwd_wave_kernel<{elt}>"
     else:

@@ -452,6 +452,9 @@ __device__ __forceinline__ void zero_empty_rows(const RowArgs& a, int first_wave
 // block: x[s] comes from memory for the first and from the L2 for the others
 // (cached loads).  A wave per token writing its k rows in turn measured slower
 // (workload of 32768 tokens, k = 4, 4 KiB rows, with drops: 168 -> 125 us).
+// U chunks per lane and step: as many as the row needs, up to kUnroll (chunks past
+// the row cost their instructions).
+template <int U>
 __global__ __launch_bounds__(kDispWaves * kWave) void dispatch_scatter_kernel(RowArgs a, int64_t pair_blocks) {
   const int lane = lane_id();
   const int wave = threadIdx.x / kWave;
@@ -474,12 +477,12 @@ __global__ __launch_bounds__(kDispWaves * kWave) void dispatch_scatter_kernel(Ro
   const int64_t row = static_cast<int64_t>(e) * a.C + slot;
   const __amdgpu_buffer_rsrc_t srow = buf_rsrc(reinterpret_cast<const u32x4*>(a.src) + s * nch, nch * 16);
   const __amdgpu_buffer_rsrc_t dst = buf_rsrc(reinterpret_cast<u32x4*>(a.dst) + row * nch, nch * 16);
-  for (int base = 0; base < nch; base += kWave * kUnroll) {
-    u32x4 v[kUnroll];
+  for (int base = 0; base < nch; base += kWave * U) {
+    u32x4 v[U];
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) v[u] = __builtin_amdgcn_raw_buffer_load_b128(srow, (base + u * kWave + lane) * 16, 0, 0);
+    for (int u = 0; u < U; ++u) v[u] = __builtin_amdgcn_raw_buffer_load_b128(srow, (base + u * kWave + lane) * 16, 0, 0);
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) buf_store_nt(v[u], dst, (base + u * kWave + lane) * 16);
+    for (int u = 0; u < U; ++u) buf_store_nt(v[u], dst, (base + u * kWave + lane) * 16);
   }
 }
 
@@ -491,10 +494,9 @@ __global__ __launch_bounds__(kDispWaves * kWave) void dispatch_scatter_kernel(Ro
 // (non-temporal).  A wave per token carrying all k dot products held ~126
 // VGPRs; a wave per choice holds ~72 (workload of 32768 tokens, k = 4, 4 KiB
 // rows: 235 -> 207 us).
-template <typename T, bool DW>
+template <typename T, bool DW, int kU>  // kU: chunks per lane per step, at most 4
 __global__ __launch_bounds__(kBwdScatterWaves * kWave) void combine_bwd_scatter_kernel(RowArgs a, int64_t pair_blocks) {
   constexpr int kEl = Chunk<T>::kElems;
-  constexpr int kU = 4;  // chunks per lane per step
   const int lane = lane_id();
   const int wave = threadIdx.x / kWave;
   if (static_cast<int64_t>(blockIdx.x) >= pair_blocks) {
@@ -625,7 +627,14 @@ hipError_t launch_dispatch(const RowArgs& a, hipStream_t st) {
     const int64_t pair_blocks = (static_cast<int64_t>(a.S) * a.k + kDispWaves - 1) / kDispWaves;
     const unsigned grid = static_cast<unsigned>(pair_blocks) + zero_blocks(a.rows, kDispWaves);
     if (grid == 0) return hipSuccess;
-    dispatch_scatter_kernel<<<dim3(grid), dim3(kDispWaves * kWave), 0, st>>>(a, pair_blocks);
+    const int need = (a.nch + kWave - 1) / kWave;
+    const dim3 g(grid), block(kDispWaves * kWave);
+    if (need == 1) dispatch_scatter_kernel<1><<<g, block, 0, st>>>(a, pair_blocks);
+    else if (need == 2) dispatch_scatter_kernel<2><<<g, block, 0, st>>>(a, pair_blocks);
+    else if (need == 3) dispatch_scatter_kernel<3><<<g, block, 0, st>>>(a, pair_blocks);
+    else if (need == 4) dispatch_scatter_kernel<4><<<g, block, 0, st>>>(a, pair_blocks);
+    else if (need <= 6 || need == 11 || need == 12) dispatch_scatter_kernel<6><<<g, block, 0, st>>>(a, pair_blocks);
+    else dispatch_scatter_kernel<kUnroll><<<g, block, 0, st>>>(a, pair_blocks);
     return hipGetLastError();
   }
   // the element type is irrelevant to a bit copy
@@ -658,7 +667,11 @@ static void launch_token_rows_t(const RowArgs& a, hipStream_t st) {
   // with three or more choices, two chunks per thread where rows split evenly
   // into waves; otherwise one
   const int cpt = (a.k >= 3 && a.nch % (2 * kWave) == 0) ? 2 : 1;
-  const int rt = a.nch / cpt;  // threads a row would take
+  int rt = a.nch / cpt;  // threads a row would take
+  // rows that are no whole waves take whole waves all the same where no fewer rows
+  // fit the block: the token of a wave is uniform then (scalar routing loads)
+  const int whole = (rt + kWave - 1) / kWave * kWave;
+  if (rt < kRowThreads && kRowThreads / whole == kRowThreads / rt) rt = whole;
   const int tpr = rt <= kRowThreads ? rt : kRowThreads;
   const int rpb = rt <= kRowThreads ? kRowThreads / rt : 1;
   if (cpt == 2) launch_token_rows_w<T, WEIGHTED, true, 2>(a, tpr, rpb, st);
@@ -678,18 +691,27 @@ hipError_t launch_combine(const RowArgs& a, bool weighted, hipStream_t st) {
   return hipGetLastError();
 }
 
+template <typename T, bool DW>
+static void launch_bwd_scatter(const RowArgs& a, int64_t pair_blocks, unsigned grid, hipStream_t st) {
+  const int need = (a.nch + kWave - 1) / kWave;
+  const dim3 g(grid), block(kBwdScatterWaves * kWave);
+  if (need == 1) combine_bwd_scatter_kernel<T, DW, 1><<<g, block, 0, st>>>(a, pair_blocks);
+  else if (need == 2) combine_bwd_scatter_kernel<T, DW, 2><<<g, block, 0, st>>>(a, pair_blocks);
+  else if (need == 3 || need == 6 || need == 5) combine_bwd_scatter_kernel<T, DW, 3><<<g, block, 0, st>>>(a, pair_blocks);
+  else combine_bwd_scatter_kernel<T, DW, 4><<<g, block, 0, st>>>(a, pair_blocks);
+}
+
 hipError_t launch_combine_bwd(const RowArgs& a, hipStream_t st) {
   if (a.k > 1) {
     const int64_t pair_blocks = (static_cast<int64_t>(a.S) * a.k + kBwdScatterWaves - 1) / kBwdScatterWaves;
     const unsigned grid = static_cast<unsigned>(pair_blocks) + zero_blocks(a.rows, kBwdScatterWaves);
     if (grid == 0) return hipSuccess;
-    const dim3 g(grid), block(kBwdScatterWaves * kWave);
     if (a.dtype == 1) {
-      if (a.dw) combine_bwd_scatter_kernel<bf16_t, true><<<g, block, 0, st>>>(a, pair_blocks);
-      else combine_bwd_scatter_kernel<bf16_t, false><<<g, block, 0, st>>>(a, pair_blocks);
+      if (a.dw) launch_bwd_scatter<bf16_t, true>(a, pair_blocks, grid, st);
+      else launch_bwd_scatter<bf16_t, false>(a, pair_blocks, grid, st);
     } else {
-      if (a.dw) combine_bwd_scatter_kernel<float, true><<<g, block, 0, st>>>(a, pair_blocks);
-      else combine_bwd_scatter_kernel<float, false><<<g, block, 0, st>>>(a, pair_blocks);
+      if (a.dw) launch_bwd_scatter<float, true>(a, pair_blocks, grid, st);
+      else launch_bwd_scatter<float, false>(a, pair_blocks, grid, st);
     }
     return hipGetLastError();
   }
