@@ -17,7 +17,11 @@ namespace hetumoe {
 // from outside the buffer resources and are zeros.  Each stage is summed on its
 // own and then added to the running sum, so rounding grows with the stages, not
 // with d / 32.  Experts past E hold
-// whatever LDS held: their columns are never read.
+// whatever LDS held: their columns are never read.  Sixteen waves and the longest
+// stage that LDS holds twice: 8192 x 4096 x 128 with two K ranges 29 us (8 waves,
+// stages of 64) -> 26, 32768 x 4096 x 128 whole gate 118 -> 97; the loads are not
+// what bounds it (one or two stages ahead: the same), the operand reads from LDS
+// are, the transpose reads above all.
 template <int NT, int WM, int WN, int KC, int DEPTH, int KMAX, int MODE>
 __global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs a) {
   constexpr int THREADS = WM * WN * kWave;
@@ -26,9 +30,9 @@ __global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs 
   constexpr int LDX = KC + 8;                          // row strides in LDS (bf16): x 16 bytes past
   constexpr int LDW = 16 * (NT + ((1 - NT) & 3));      // whole banks, W rows 32 bytes past 128
   constexpr int LGS = tile_lgs(NT);
-  constexpr int XP = kTileTok * KC / 8 / THREADS;      // 16-byte pieces per thread and stage
+  constexpr int XN = kTileTok * KC / 8;                // 16-byte pieces of x per stage
+  constexpr int XP = (XN + THREADS - 1) / THREADS;     // and per thread
   constexpr int WP = (KC * 16 * NT / 8 + THREADS - 1) / THREADS;
-  static_assert(XP * THREADS * 8 == kTileTok * KC, "whole x pieces");
   constexpr int kStage = (kTileTok * LDX + KC * LDW) * 2;
   constexpr int kLg = kTileTok * LGS * 4;
   __shared__ __align__(16) unsigned char raw[2 * kStage > kLg ? 2 * kStage : kLg];
@@ -61,7 +65,7 @@ __global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs 
     for (int i = 0; i < XP; ++i) {
       const int p = tid + i * THREADS;
       const int t = p / (KC / 8), col = kc + 8 * (p % (KC / 8));
-      xr[i] = tile_load(xsrc, col < kend ? (t * d + col) * 2 : kTileOob);
+      xr[i] = tile_load(xsrc, (XN % THREADS == 0 || p < XN) && col < kend ? (t * d + col) * 2 : kTileOob);
     }
 #pragma unroll
     for (int i = 0; i < WP; ++i) {
@@ -75,16 +79,19 @@ __global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs 
 #pragma unroll
     for (int i = 0; i < XP; ++i) {
       const int p = tid + i * THREADS;
+      if (XN % THREADS != 0 && p >= XN) continue;
       *reinterpret_cast<u32x4*>(&xs[(p / (KC / 8)) * LDX + 8 * (p % (KC / 8))]) = xr[i];
     }
+    if (E % 8 == 0) {
 #pragma unroll
-    for (int i = 0; i < WP; ++i) {
-      if (tid + i * THREADS >= wcnt) continue;
-      if (E % 8 == 0) {
-        *reinterpret_cast<u32x4*>(&ws[tr_row(wrow[i]) * LDW + wcol[i]]) = wr[i];
-      } else {
-        // the piece crosses rows of W: element pairs where E is even, single
-        // elements where it is odd
+      for (int i = 0; i < WP; ++i)
+        if (tid + i * THREADS < wcnt) *reinterpret_cast<u32x4*>(&ws[tr_row(wrow[i]) * LDW + wcol[i]]) = wr[i];
+    } else {
+      // the pieces cross rows of W: element pairs where E is even, single elements
+      // where it is odd
+#pragma unroll
+      for (int i = 0; i < WP; ++i) {
+        if (tid + i * THREADS >= wcnt) continue;
         int r = wrow[i], c = wcol[i];
         if (E % 2 == 0) {
 #pragma unroll
@@ -145,10 +152,6 @@ __global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs 
   // is multiplied; one barrier per stage.  A range's sums start from zero and
   // ranges are added in order, so a block that takes all of them gives the same
   // logits as blocks that take one each.
-  // Of the two waves that a SIMD holds of an eight-wave block, one stages before it
-  // multiplies and one after, so that one's LDS writes meet the other's products
-  // (all waves are at the same stage).
-  const bool early = __builtin_amdgcn_readfirstlane(w) < 4;
   const int z0 = MODE == kTilePart ? blockIdx.y : 0;
   const int z1 = MODE == kTilePart ? z0 + 1 : a.zsplit;
   for (int z = z0; z < z1; ++z) {
@@ -166,16 +169,10 @@ __global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs 
 #pragma unroll
       for (int q = 1; q <= DEPTH; ++q) {
         const int set = q % DEPTH;
-        if (early) {
-          stage(xq[set], wq[set], buf ^ 1);
-          load(xq[set], wq[set], kc + (DEPTH + 1) * KC, kend);
-          __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the products
-        }
+        stage(xq[set], wq[set], buf ^ 1);
+        load(xq[set], wq[set], kc + (DEPTH + 1) * KC, kend);
+        __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the products
         multiply(buf);
-        if (!early) {
-          stage(xq[set], wq[set], buf ^ 1);
-          load(xq[set], wq[set], kc + (DEPTH + 1) * KC, kend);
-        }
         __syncthreads();
         buf ^= 1;
         kc += KC;

@@ -7,7 +7,7 @@ hipError_t launch_route_tile_bf16_small(const RouteArgs& a, hipStream_t st) {
   if (a.E <= 16) return tile_by_gate(a, TileBf16Launch<1, 4, 1, 128, 1>{a, st});
   if (a.E <= 32) return tile_by_gate(a, TileBf16Launch<2, 4, 2, 128, 1>{a, st});
   if (a.E <= 48) return tile_by_gate(a, TileBf16Launch<3, 4, 1, 128, 1>{a, st});
-  return tile_by_gate(a, TileBf16Launch<4, 4, 2, 128, 1>{a, st});
+  return tile_by_gate(a, TileBf16Launch<4, 4, 4, 128, 1>{a, st});
 }
 
 }  // namespace hetumoe
