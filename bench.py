@@ -193,7 +193,7 @@ def summarize_route(args):
         out = []
         for r in rows:
             name = r["Name"].replace("void ", "").replace("hetumoe::", "").split("(")[0]
-            if name.startswith(("route_", "scan_", "assign_", "scan_assign", "select_ext")):
+            if name.startswith(("route_", "group_scan", "assign_", "select_")):
                 out.append((name, int(r["Calls"]), float(r["AverageNs"])))
         if not out:
             raise SystemExit(f"no gate kernels in {d}")

@@ -151,7 +151,11 @@ MOE_API moe_status moe_gate_workspace_size(const moe_gate_params* p, size_t* byt
  *          skip), slot_src [E,C] (s*k + r of the assignment in each slot, -1 if
  *          empty).  Dropped assignments still report their id and weight.
  * Workspace device memory of at least moe_gate_workspace_size() bytes, 16-byte
- *          aligned; contents on entry are ignored.
+ *          aligned; contents on entry are ignored.  Small batches of wide rows
+ *          split the projection over blocks and report room for its partial
+ *          logits; a workspace without that room (the histogram, 4 * k * E *
+ *          ceil(S/64) bytes, plus 4 * S * E for the Dense-To-Sparse and
+ *          hierarchical gates) is accepted and gives the same logits, slower.
  */
 MOE_API moe_status moe_gate(const moe_gate_params* p, const void* x, const void* wg,
                     const float* bias, const int32_t* token_ids, const float* noise,
@@ -171,11 +175,12 @@ MOE_API moe_status moe_gate(const moe_gate_params* p, const void* x, const void*
  * first call on that GPU until the process ends; the call itself allocates
  * nothing (no hipMalloc, no allocating library routine).
  *
- * Limit    the workspace moe_gate_workspace_size() reports for `p` must be at
- *          most MOE_GATE_NOALLOC_MAX_BYTES (the histogram, 4 * k * E * ceil(S/64)
- *          bytes, plus S * E * 4 bytes of logits for the Dense-To-Sparse and
- *          hierarchical gates that select in a kernel of their own); larger
- *          requests return MOE_ERR_UNSUPPORTED before any HIP call.
+ * Limit    the histogram, 4 * k * E * ceil(S/64) bytes, plus S * E * 4 bytes of
+ *          logits for the Dense-To-Sparse and hierarchical gates, must fit
+ *          MOE_GATE_NOALLOC_MAX_BYTES; larger requests return
+ *          MOE_ERR_UNSUPPORTED before any HIP call.  (What
+ *          moe_gate_workspace_size() reports may be more: the partial logits of
+ *          a split projection, which is taken only where they fit too.)
  * Scratch  every call on one GPU uses that GPU's one array: calls that overlap
  *          on one GPU (several streams or host threads at once) race and give
  *          undefined results.  Calls in order on one stream are safe; no

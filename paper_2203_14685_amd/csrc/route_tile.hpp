@@ -76,8 +76,7 @@ __device__ __forceinline__ void tile_epilogue(const RouteArgs& a, float* lg, int
   for (int i = tid; i < a.k * E; i += THREADS) a.hist[static_cast<int64_t>(blockIdx.x) * a.k * E + i] = hist_lds[i];
 }
 
-// The block's partial sums of one K range into its plane.  put(row, expert, v)
-// is called by `each` for every accumulator the lane holds.
+// Where the block's partial sums of its K range go: its 64 rows of its plane.
 __device__ __forceinline__ float* tile_plane(const RouteArgs& a) {
   return a.part + static_cast<int64_t>(blockIdx.y) * a.S * a.E + static_cast<int64_t>(blockIdx.x) * kTileTok * a.E;
 }
