@@ -230,7 +230,7 @@ __global__ __launch_bounds__(WM* WN * 64) void dwg_tile_bf16_kernel(GateBwdArgs 
 // transposed (W rows are the A operand) and regrouped by lane swaps so that one
 // store covers 8 tokens x 128 bytes, as in dx_mfma_kernel.
 // W fragments are read ahead of their products and nothing waits for stores: the
-// whole gate backward of 8192 x 4096, E = 256, 152.3 -> 146.1 us (this kernel 59 -> 53).
+// whole gate backward of 8192 x 4096, E = 256, 152.3 -> 146.1 us (this kernel 59 -> 52).
 constexpr int kDxWaves = 8;
 constexpr int kDxThreads = kDxWaves * kWave;
 
@@ -609,9 +609,8 @@ __global__ __launch_bounds__(kDxThreads) void dx_tile_f32_kernel(GateBwdArgs a, 
   const int d = a.d, E = a.E;
   const int CB = PC * passes;
   const int ncb = (d + CB - 1) / CB;
-  const int64_t sblk = static_cast<int64_t>(blockIdx.x / ncb) * (16 * kDxWaves);
-  const int64_t sm = sblk + 16 * w + m;
-  const int jb = static_cast<int>(blockIdx.x % ncb) * CB;
+  const int64_t sblk = static_cast<int64_t>(uniform(blockIdx.x / ncb)) * (16 * kDxWaves);
+  const int jb = uniform(blockIdx.x % ncb) * CB;
   uint32_t dv[KQ][4];
   {
     const int rows = static_cast<int>(min(static_cast<int64_t>(16 * kDxWaves), a.S - sblk));
@@ -663,7 +662,11 @@ __global__ __launch_bounds__(kDxThreads) void dx_tile_f32_kernel(GateBwdArgs a, 
       wl[r / PC][(r % PC) * LDW + E + i % n] = 0.f;
     }
   }
-  float* dx = reinterpret_cast<float*>(a.dx);
+  // dx without a branch, as in dx_tile_bf16_kernel (8192 x 2048, E = 64: 29.7 -> 28.1 us)
+  const int64_t s0 = sblk + 16 * uniform(w);
+  const int dxn = uniform(s0 < a.S ? static_cast<int>(min(static_cast<int64_t>(16), a.S - s0)) : 0);
+  const __amdgpu_buffer_rsrc_t dxr =
+      rsrc_of(reinterpret_cast<float*>(a.dx) + (dxn > 0 ? s0 * d : 0), static_cast<unsigned>(dxn) * d * 4u);
   const int arow = 8 * (m / 4) + m % 4;  // column of A row m in tile 0 of a pair; tile 1 is 4 on
   const bool early = (__builtin_amdgcn_readfirstlane(w) & 4) == 0;
   int buf = 0;
@@ -680,13 +683,12 @@ __global__ __launch_bounds__(kDxThreads) void dx_tile_f32_kernel(GateBwdArgs a, 
 #pragma unroll
     for (int pr = 0; pr < PC / 32; ++pr) {
       const int j = j0 + 32 * pr + 8 * g;
-      f32x4 in[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-      const bool ok = sm < a.S && j < d;         // d and j: multiples of 4
-      const bool ok1 = ok && j + 4 < d;
-      float* o = dx + sm * d + j;
+      const bool ok = m < dxn && j < d;  // d and j: multiples of 4
+      const int off[2] = {ok ? (m * d + j) * 4 : kOob, ok && j + 4 < d ? (m * d + j + 4) * 4 : kOob};
+      u32x4 in[2];
       if constexpr (ACC) {
-        if (ok) in[0] = *reinterpret_cast<const f32x4*>(o);
-        if (ok1) in[1] = *reinterpret_cast<const f32x4*>(o + 4);
+        in[0] = load16(dxr, off[0]);
+        in[1] = load16(dxr, off[1]);
       }
       f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
@@ -703,8 +705,11 @@ __global__ __launch_bounds__(kDxThreads) void dx_tile_f32_kernel(GateBwdArgs a, 
             acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(wf, __uint_as_float(dv[q][i]), acc[u], 0, 0, 0);
           }
       }
-      if (ok) *reinterpret_cast<f32x4*>(o) = acc[0] + in[0];
-      if (ok1) *reinterpret_cast<f32x4*>(o + 4) = acc[1] + in[1];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        if constexpr (ACC) acc[u] += __builtin_bit_cast(f32x4, in[u]);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc[u]), dxr, off[u], 0, 0);
+      }
     }
     if (!early) {
       stage_w(wl[buf ^ 1]);
