@@ -70,8 +70,8 @@ struct SelectArgs {
   const float* raw;        // [planes, S, E]
   const float* bias;       // [E] or null
   const float* noise;      // [S, E] or null
-  float* fin;              // [S, E] final logits or null; required past kSelectTileE experts
-                           // unless they are raw itself
+  float* fin;              // [S, E] final logits or null; required past kSelectTileE experts,
+                           // where it may be raw itself: raw then becomes the final logits
   int32_t* ids;            // [S, k]
   float* weights;          // [S, k]
   int32_t* hist;           // [nb, k, E]

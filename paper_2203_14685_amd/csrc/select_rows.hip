@@ -9,7 +9,7 @@ namespace hetumoe {
 // bias and the noise, divides by the temperature, stores the final logits when
 // asked and keeps them in LDS, four (V4: 16-byte) pieces in flight per thread.
 // Rows of more than kSelectTileE experts stay in memory: the selection reads
-// them from there.
+// them from a.fin, written here unless they are a.raw as it is.
 template <int P, int KMAX, int MODE, bool V4>  // MODE: 0 top-k, 1 kTop1, 3 hierarchical top-k
 __global__ __launch_bounds__(kWave * P) void select_rows_kernel(SelectArgs a, int lgs) {
   extern __shared__ __align__(16) float lds[];  // [64][lgs] logits (lgs > 0), then [k][E] counts
@@ -21,7 +21,11 @@ __global__ __launch_bounds__(kWave * P) void select_rows_kernel(SelectArgs a, in
   const int64_t base = static_cast<int64_t>(blockIdx.x) * kWave * E;
   int* hist_lds = reinterpret_cast<int*>(lds + kWave * lgs);
   for (int i = threadIdx.x; i < a.k * E; i += kThreads) hist_lds[i] = 0;
-  if (lgs > 0 || a.fin != a.raw) {
+  // a.fin may be a.raw: a thread then overwrites only elements that no other thread
+  // uses (past the last row it reads the block's first element and drops it)
+  const bool changed = a.planes > 1 || a.bias || a.temperature > 0.f;
+  const bool store = a.fin && (a.fin != a.raw || (changed && lgs == 0));
+  if (lgs > 0 || store) {
     const int rows = static_cast<int>(min(static_cast<int64_t>(kWave), a.S - static_cast<int64_t>(blockIdx.x) * kWave));
     const int n = E / kVec;  // pieces per row
     const int dr = kThreads / n, dc = kThreads - dr * n;
@@ -74,7 +78,7 @@ __global__ __launch_bounds__(kWave * P) void select_rows_kernel(SelectArgs a, in
             v[u][q] = scale != 0.f ? x * scale : x / a.temperature;
           }
         }
-        if (a.fin && a.fin != a.raw) {
+        if (store) {
           float* f = a.fin + base + ru[u] * E + cu[u];
           if constexpr (V4) *reinterpret_cast<float4*>(f) = float4{v[u][0], v[u][1], v[u][2], v[u][3]};
           else *f = v[u][0];
