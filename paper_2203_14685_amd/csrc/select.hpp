@@ -327,16 +327,18 @@ struct KeyList {
   }
 };
 
-// Sum of exp(logit - top) over the experts [lo, hi), by all P lanes.
-template <int P>
-__device__ __forceinline__ float row_expsum(const float* lrow, int lo, int hi, int j, float top) {
+// Sum of exp(logit - top) over the experts [lo, hi), by all P lanes.  BEST: expert
+// `best`, whose logit top is, counts exp(0) = 1 also where it is infinite.
+template <int P, bool BEST>
+__device__ __forceinline__ float row_expsum(const float* lrow, int lo, int hi, int j, float top, int best) {
   float s = 0.f;
   for (int e = lo + j; e < hi; e += 4 * P) {
     float v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) v[u] = lrow[min(e + u * P, hi - 1)];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) s += e + u * P < hi ? __expf(v[u] - top) : 0.f;
+    for (int u = 0; u < 4; ++u)
+      s += e + u * P >= hi ? 0.f : BEST && e + u * P == best ? 1.f : __expf(v[u] - top);
   }
   return group_reduce<P>(s, OpAdd());
 }
@@ -383,7 +385,7 @@ __device__ __forceinline__ void select_row(const float* lrow, int E, int k, int 
       best.template scan<P>(lrow, lo, hi, j);
       int key, id;
       best.template pop<P, 0>(key, id);
-      const float z = row_expsum<P>(lrow, lo, hi, j, key_logit(key));
+      const float z = row_expsum<P, true>(lrow, lo, hi, j, key_logit(key), id);
       if (valid && j == grp % P) {
         ids[grp] = id;
         weights[grp] = 1.f / z;
@@ -413,7 +415,7 @@ __device__ __forceinline__ void select_row(const float* lrow, int E, int k, int 
       for (int r = 0; r < KMAX; ++r)
         if (r < k) z += __expf(key_logit(key[r]) - top);
     } else {
-      z = row_expsum<P>(lrow, 0, E, j, top);
+      z = row_expsum<P, false>(lrow, 0, E, j, top, 0);
     }
     write_choices<P, KMAX>(key, id, top, 1.f / z, k, E, j, valid, ids, weights, hist_lds);
   }
