@@ -50,6 +50,23 @@ __device__ __forceinline__ void split_trunc(float v, uint32_t& h, uint32_t& m, u
   m = __float_as_uint(r1) & 0xffff0000u;
   l = __float_as_uint(r1 - __uint_as_float(m));
 }
+// The same for N values of which some may be infinite: hi is the value itself
+// then, and mid and lo, inf - inf, are made 0 (one test for all N: |v| is rarely
+// that large).  NaN stays in all three.
+template <int N>
+__device__ __forceinline__ void split_trunc_n(const uint32_t* v, uint32_t* h, uint32_t* m, uint32_t* l) {
+  float top = 0.f;
+#pragma unroll
+  for (int q = 0; q < N; ++q) {
+    split_trunc(__uint_as_float(v[q]), h[q], m[q], l[q]);
+    top = fmaxf(top, fabsf(__uint_as_float(v[q])));
+  }
+  if (top == INFINITY) {
+#pragma unroll
+    for (int q = 0; q < N; ++q)
+      if (fabsf(__uint_as_float(v[q])) == INFINITY) m[q] = l[q] = 0u;
+  }
+}
 __device__ __forceinline__ uint32_t pack_hi(uint32_t a, uint32_t b) { return (a >> 16) | (b & 0xffff0000u); }
 
 // Row stride in LDS (bf16 elements) of rows of 16 n: an odd multiple of 32 bytes,
@@ -128,12 +145,9 @@ __global__ __launch_bounds__(WM* WN * 64) void dwg_tile_bf16_kernel(GateBwdArgs 
 #pragma unroll
     for (int i = 0; i < LP; ++i) {
       if (tid + i * THREADS >= lcnt) continue;
+      const uint32_t u[4] = {lr[i].x, lr[i].y, lr[i].z, lr[i].w};
       uint32_t h[4], md[4], lo[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const uint32_t u = lr[i][q];
-        split_trunc(__uint_as_float(u), h[q], md[q], lo[q]);
-      }
+      split_trunc_n<4>(u, h, md, lo);
       if (E % 4 == 0) {
         uint16_t* o = &pl[buf][tr_row(lrow[i]) * LDE + lcol[i]];
         *reinterpret_cast<uint2*>(o) = uint2{pack_hi(h[0], h[1]), pack_hi(h[2], h[3])};
@@ -277,8 +291,7 @@ __global__ __launch_bounds__(kDxThreads) void dx_tile_bf16_kernel(GateBwdArgs a,
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       uint32_t h[8], md[8], lo[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) split_trunc(__uint_as_float(v[ks][q]), h[q], md[q], lo[q]);
+      split_trunc_n<8>(v[ks], h, md, lo);
       ph[ks] = u32x4{pack_hi(h[0], h[1]), pack_hi(h[2], h[3]), pack_hi(h[4], h[5]), pack_hi(h[6], h[7])};
       pm[ks] = u32x4{pack_hi(md[0], md[1]), pack_hi(md[2], md[3]), pack_hi(md[4], md[5]), pack_hi(md[6], md[7])};
       pq[ks] = u32x4{pack_hi(lo[0], lo[1]), pack_hi(lo[2], lo[3]), pack_hi(lo[4], lo[5]), pack_hi(lo[6], lo[7])};
