@@ -85,7 +85,7 @@ hipError_t launch_route_tile_f32(const RouteArgs& a, hipStream_t st);
 bool route_uses_tile_bf16(const RouteArgs& a);
 bool route_uses_tile_f32(const RouteArgs& a);
 // K ranges of the tiled routes: how many (1 unless the batch alone leaves CUs
-// idle) and how long.
+// idle, and for shapes that another kernel serves) and how long.
 struct TileSplit {
   int z, cols;
 };
@@ -94,6 +94,12 @@ hipError_t launch_route_mfma_rs(const RouteArgs& a, int cus, hipStream_t st);
 // Compute units of the current device (queried once per device).
 int device_cu_count();
 bool route_uses_mfma_rs(const RouteArgs& a);
+// Shapes it serves, all with eight waves: bf16, E in {16, 32, 64, 128}, d in {512,
+// 1024, 2048}, with d * E <= 131072.
+inline bool route_mfma_rs_shape(int dtype, int E, int d) {
+  return dtype == 1 && (E == 16 || E == 32 || E == 64 || E == 128) && (d == 512 || d == 1024 || d == 2048) &&
+         static_cast<int64_t>(d) * E <= 131072;
+}
 // True when a matrix-core route kernel takes this projection: it then also
 // applies the noise and temperature and the hierarchical top-k itself, so the
 // extended gates need no logits round trip.

@@ -216,14 +216,9 @@ static hipError_t launch_rs_nt(const RouteArgs& a, int grid, hipStream_t st) {
   return launch_rs_t<WAVES, NT, KSL, 8, 0>(a, grid, st);
 }
 
-// Shapes served: bf16, E in {16, 32, 64, 128}, d in {512, 1024, 2048}, with
-// d * E <= 131072, all with eight waves.
 bool route_uses_mfma_rs(const RouteArgs& a) {
-  if (a.kind == 2 || a.dtype != 1) return false;
-  if (a.E != 16 && a.E != 32 && a.E != 64 && a.E != 128) return false;
-  if (a.d != 512 && a.d != 1024 && a.d != 2048) return false;
-  if (static_cast<int64_t>(a.d) * a.E > 131072) return false;
-  return (reinterpret_cast<uintptr_t>(a.x) % 16) == 0 && (reinterpret_cast<uintptr_t>(a.wg) % 16) == 0;
+  return a.kind != 2 && route_mfma_rs_shape(a.dtype, a.E, a.d) && (reinterpret_cast<uintptr_t>(a.x) % 16) == 0 &&
+         (reinterpret_cast<uintptr_t>(a.wg) % 16) == 0;
 }
 
 hipError_t launch_route_mfma_rs(const RouteArgs& a, int cus, hipStream_t st) {

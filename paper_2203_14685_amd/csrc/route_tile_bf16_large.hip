@@ -16,9 +16,11 @@ hipError_t launch_route_tile_bf16(const RouteArgs& a, hipStream_t st) {
 bool route_uses_tile_bf16(const RouteArgs& a) { return a.dtype == 1 && tile_shape(a); }
 
 TileSplit route_tile_split(int S, int d, int E, int dtype) {
-  constexpr int kBlocks = 256;  // one block per CU
+  // one block per CU of a whole gfx950; a constant, so that the workspace size and
+  // with it a batch's logits are the same on every device and need no device query
+  constexpr int kBlocks = 256;
   constexpr int kRange = 256;   // columns: whole stages of every tile shape
-  if (E > kTileMaxE) return {1, d > 0 ? d : 1};
+  if (E > kTileMaxE || route_mfma_rs_shape(dtype, E, d)) return {1, d > 0 ? d : 1};
   const int nb = (S + kTileTok - 1) / kTileTok;
   int z = nb > 0 ? kBlocks / nb : 1;
   z = z < 16 ? z : 16;

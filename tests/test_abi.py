@@ -63,6 +63,20 @@ def test_workspace_size(lib, S, E, k, kind):
     assert n == k * ((S + 63) // 64) * E * 4
 
 
+@pytest.mark.parametrize("S,d,E,k,planes", [
+    # shapes whose W stays in registers never split K and ask for the histogram alone
+    (32, 2048, 64, 2, 0), (2048, 2048, 64, 2, 0), (700, 512, 16, 2, 0), (4096, 1024, 128, 1, 0), (64, 512, 32, 8, 0),
+    # tiled shapes: up to 16 ranges of a multiple of 256 columns (1400: two of 512, one of 376), one once the batch
+    # fills the chip
+    (32, 2048, 128, 2, 8), (32, 4096, 64, 2, 16), (100, 1400, 60, 3, 3), (8192, 4096, 256, 8, 2), (8257, 4096, 256, 8, 0),
+    (32, 504, 60, 1, 0),
+])
+def test_workspace_of_split_projections(lib, S, d, E, k, planes):
+    hist = k * ((S + 63) // 64) * E * 4
+    want = (hist + 255) // 256 * 256 + planes * S * E * 4 if planes else hist
+    assert _ws(hm.gate_params(S, d, E, k, 10, 0, 0, 0, hm.MOE_BF16)) == (0, want)
+
+
 BAD_PARAMS = [
     dict(E=0), dict(E=1025), dict(S=-1), dict(capacity=-1), dict(k=0), dict(k=9, E=16),
     dict(k=3, E=2), dict(kind=1, k=3, E=16), dict(kind=2, k=2), dict(kind=3), dict(dtype=2),
