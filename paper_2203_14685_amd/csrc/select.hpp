@@ -330,7 +330,7 @@ struct KeyList {
 // Sum of exp(logit - top) over the experts [lo, hi), by all P lanes.  BEST: expert
 // `best`, whose logit top is, counts exp(0) = 1 also where it is infinite.
 template <int P, bool BEST>
-__device__ __forceinline__ float row_expsum(const float* lrow, int lo, int hi, int j, float top, int best) {
+__device__ __forceinline__ float row_expsum(const float* lrow, int lo, int hi, int j, float top, int best = 0) {
   float s = 0.f;
   for (int e = lo + j; e < hi; e += 4 * P) {
     float v[4];
@@ -385,7 +385,11 @@ __device__ __forceinline__ void select_row(const float* lrow, int E, int k, int 
       best.template scan<P>(lrow, lo, hi, j);
       int key, id;
       best.template pop<P, 0>(key, id);
-      const float z = row_expsum<P, true>(lrow, lo, hi, j, key_logit(key), id);
+      const float top = key_logit(key);
+      // the sum that tests every term for `best` only where it matters (65536 x 192, k
+      // = 2, whole gate: tested always 39.6 us, so 38.2)
+      const float z = fabsf(top) == INFINITY ? row_expsum<P, true>(lrow, lo, hi, j, top, id)
+                                             : row_expsum<P, false>(lrow, lo, hi, j, top);
       if (valid && j == grp % P) {
         ids[grp] = id;
         weights[grp] = 1.f / z;
@@ -415,7 +419,7 @@ __device__ __forceinline__ void select_row(const float* lrow, int E, int k, int 
       for (int r = 0; r < KMAX; ++r)
         if (r < k) z += __expf(key_logit(key[r]) - top);
     } else {
-      z = row_expsum<P, false>(lrow, 0, E, j, top, 0);
+      z = row_expsum<P, false>(lrow, 0, E, j, top);
     }
     write_choices<P, KMAX>(key, id, top, 1.f / z, k, E, j, valid, ids, weights, hist_lds);
   }

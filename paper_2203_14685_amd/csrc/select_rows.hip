@@ -236,7 +236,14 @@ hipError_t launch_select_rows(const SelectArgs& a, hipStream_t st) {
     if (a.E <= 192) return launch_topk_p<16, 3>(a, st);
     return launch_topk_p<16, 4>(a, st);
   }
-  return a.E <= 32 ? launch_rows_p<4>(a, st) : launch_rows_p<16>(a, st);
+  // Four lanes per token up to 32 experts, and up to 128 where more than one block
+  // per CU would wait for its turn: sixteen lanes finish a block sooner, four leave
+  // the chip more of them.  Whole gate on given logits, us, four / sixteen lanes:
+  // 16448 x 60 (257 blocks), kTop1 k = 4 15.5 / 22.5; 262144 x 60 46.6 / 128; 262144 x
+  // 100, hierarchical 44.3 / 91.7; one float at a time, 20000 x 127, k = 2 20.3 / 18.7,
+  // 65536 x 127 25.3 / 27.3.
+  const bool four = a.E <= 32 || (a.E <= 128 && a.nb > (a.E <= 64 || rows_aligned(a) ? 256 : 512));
+  return four ? launch_rows_p<4>(a, st) : launch_rows_p<16>(a, st);
 }
 
 }  // namespace hetumoe

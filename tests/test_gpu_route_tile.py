@@ -99,6 +99,9 @@ def test_split_and_one_block_give_the_same_logits(dtype, S, d, E):
 @pytest.mark.parametrize("S,E,k,kind,groups,tau", [
     (64, 32, 2, 0, 0, 0.0), (65, 33, 8, 0, 0, 0.0), (130, 256, 8, 0, 0, 0.5), (100, 257, 3, 0, 0, 0.5), (63, 255, 5, 1, 0, 0.0),
     (200, 1024, 8, 3, 4, 0.25), (1, 7, 7, 0, 0, 0.0), (129, 1023, 3, 1, 0, 0.0),
+    # four lanes per token past 32 experts: 257 wave blocks and one fewer, 513 where a row is no whole 16-byte pieces
+    (16384, 60, 4, 1, 0, 0.5), (16385, 60, 4, 1, 0, 0.5), (16385, 33, 3, 3, 3, 0.0), (16400, 128, 2, 3, 4, 0.25),
+    (16390, 128, 8, 1, 0, 0.0), (32768, 127, 2, 0, 0, 0.0), (32769, 127, 1, 1, 0, 0.0),
 ])
 def test_selection_on_given_logits(S, E, k, kind, groups, tau):
     announce(f"selection S={S} E={E} k={k} kind={kind} groups={groups} tau={tau}")
