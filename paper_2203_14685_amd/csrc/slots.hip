@@ -119,11 +119,23 @@ __global__ __launch_bounds__(T) void assign_kernel(AssignArgs a, int F) {
     }
   }
   __syncthreads();
+  // few columns leave many partial sums per column: halved until eight are left (all
+  // of them added by one thread: hash gate, 65536 tokens, E = 8 8.9 us, so 8.2)
+  int parts = G;
+  while (parts > 8) {
+    const int half = (parts + 1) / 2;
+    if (g + half < parts) {
+      part[tid] += part[tid + half * Q];
+      part[T + tid] += part[T + tid + half * Q];
+    }
+    parts = half;
+    __syncthreads();
+  }
   int first = 0;  // column tid (Q <= T): sum of the rows before the block's own
   if (tid < Q && Q <= T) {
     if (G > 1) {
       int t = 0;
-      for (int i = 0; i < G; ++i) {
+      for (int i = 0; i < parts; ++i) {
         t += part[i * Q + tid];
         first += part[T + i * Q + tid];
       }
@@ -179,7 +191,11 @@ hipError_t launch_assign(const AssignArgs& a, hipStream_t st) {
   const int64_t Q = static_cast<int64_t>(a.k) * a.E;
   // Whole gate on given logits, us.  Four wave blocks per block once there are 512
   // (four / one): S = 32768, E = 64, k = 1 15.5 / 17.8; 16384, 128, 4 18.4 / 17.5.
-  const int WB = a.nb >= 512 && Q <= 2048 ? 4 : 1;
+  // Sixteen once four would leave more blocks than the chip holds at a time, sooner
+  // at k = 1, where a block of four places its tokens with four of sixteen waves
+  // (sixteen / four): hash gate, 524288 tokens, E = 8 21 / 33, 200000, E = 64 14.4 / 20.0;
+  // 131072, E = 256 16.9 / 19.1.
+  const int WB = a.nb > (a.k == 1 ? 1024 : 2048) && Q <= 512 ? 16 : a.nb >= 512 && Q <= 2048 ? 4 : 1;
   // Counts as they are while a block adds up to 32 K of them, else groups of at
   // least 16 rows first (one launch / two): 16384, 64, 2 (32 K) 13.4 / 14.8; 16384,
   // 64, 3 (48 K) 16.4 / 15.2; 16384, 64, 4 (64 K) 17.7 / 15.7; 32768, 64, 4 (128 K)
@@ -197,7 +213,8 @@ hipError_t launch_assign(const AssignArgs& a, hipStream_t st) {
   // a few counts only: small blocks start sooner
   if (Q <= 256 && a.k <= 4 && Q * a.nb <= 4096) launch_assign_t<256, 1>(a, F, st);
   else if (WB == 1) launch_assign_t<1024, 1>(a, F, st);
-  else launch_assign_t<1024, 4>(a, F, st);
+  else if (WB == 4) launch_assign_t<1024, 4>(a, F, st);
+  else launch_assign_t<1024, 16>(a, F, st);
   return hipGetLastError();
 }
 

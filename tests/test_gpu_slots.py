@@ -42,6 +42,9 @@ def reference(ids, E, C):
     (300, 200, 8), (8000, 1024, 8),                                        # more columns than threads
     (32705, 60, 1), (32833, 64, 1), (33000, 16, 8), (33001, 512, 8),       # four wave blocks per block, ragged
     (128001, 128, 8),                                                      # groups of 64 rows
+    (65536, 5, 1), (65600, 5, 1), (65601, 300, 1), (131072, 3, 2), (131073, 3, 2),  # sixteen wave blocks per block
+    (131200, 64, 8), (131200, 65, 8),                                      # 512 columns, and too many for sixteen
+    (200, 2, 1), (4000, 1, 1), (2100, 3, 3),                               # many partial sums per column
 ])
 def test_slots(S, E, k):
     announce(f"slots S={S} E={E} k={k}")
