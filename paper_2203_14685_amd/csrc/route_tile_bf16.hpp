@@ -14,19 +14,24 @@ namespace hetumoe {
 // fragments are 16-byte LDS reads of x, B fragments (8 consecutive K of one
 // expert) transpose reads of W.  The next stage is loaded into registers while
 // the current one is multiplied; columns past d and rows past the batch come
-// from outside the buffer resources and are zeros.  Each stage is summed on its
-// own and then added to the running sum, so rounding grows with the stages, not
-// with d / 32.  Experts past E hold
-// whatever LDS held: their columns are never read.  Sixteen waves and the longest
-// stage that LDS holds twice: 8192 x 4096 x 128 with two K ranges 29 us (8 waves,
+// from outside the buffer resources and are zeros.  Each kSum columns are summed on
+// their own and then added to the running sum, so rounding grows with their number,
+// not with d / 32.  Experts past E hold whatever LDS held: their columns are never
+// read.  Sixteen waves and the longest stage that LDS holds twice: 8192 x 4096 x 128 with two K ranges 29 us (8 waves,
 // stages of 64) -> 26, 32768 x 4096 x 128 whole gate 118 -> 97; the loads are not
 // what bounds it (one or two stages ahead: the same), the operand reads from LDS
 // are, the transpose reads above all.
-template <int NT, int WM, int WN, int KC, int DEPTH, int KMAX, int MODE>
-__global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs a) {
+// ONE: the launch has one K range, so no sum over ranges is held (at 16 tiles the
+// registers it takes went to scratch), and at most 128 registers; with stages
+// of 64 two blocks of eight waves share a CU then (tile_two_per_cu).  Same sums
+// either way.
+template <int NT, int WM, int WN, int KC, int DEPTH, bool ONE, int KMAX, int MODE>
+__global__ __launch_bounds__(WM* WN * 64) __attribute__((amdgpu_waves_per_eu(ONE ? 4 : WM * WN / 4)))
+void route_tile_bf16_kernel(RouteArgs a) {
   constexpr int THREADS = WM * WN * kWave;
   constexpr int MT = 4 / WM, NTW = NT / WN;  // 16 x 16 tiles per wave
   static_assert(MT * WM == 4 && NTW * WN == NT, "whole tiles per wave");
+  constexpr int kSum = NT > 8 ? 64 : 128;              // columns summed on their own, whatever KC is
   constexpr int LDX = KC + 8;                          // row strides in LDS (bf16): x 16 bytes past
   constexpr int LDW = 16 * (NT + ((1 - NT) & 3));      // whole banks, W rows 32 bytes past 128
   constexpr int LGS = tile_lgs(NT);
@@ -112,15 +117,10 @@ __global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs 
     }
   };
 
-  f32x4 rsum[MT][NTW], sum[MT][NTW];
+  f32x4 rsum[MT][NTW], sum[MT][NTW], acc[MT][NTW];
   auto multiply = [&](int buf) {
     const uint16_t* xs = reinterpret_cast<const uint16_t*>(raw + buf * kStage);
     const uint16_t* ws = xs + kTileTok * LDX;
-    f32x4 acc[MT][NTW];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-      for (int nt = 0; nt < NTW; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ks = 0; ks < KC / 32; ++ks) {
       u32x4 av[MT];
@@ -142,10 +142,15 @@ __global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs 
                                                                 __builtin_bit_cast(bf16x8, bv), acc[mt][nt], 0, 0, 0);
       }
     }
+  };
+  auto flush = [&]() {
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-      for (int nt = 0; nt < NTW; ++nt) rsum[mt][nt] += acc[mt][nt];
+      for (int nt = 0; nt < NTW; ++nt) {
+        rsum[mt][nt] += acc[mt][nt];
+        acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
   };
 
   // Stage s + 1 goes to LDS and stage s + 1 + DEPTH is requested while stage s
@@ -153,13 +158,13 @@ __global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs 
   // ranges are added in order, so a block that takes all of them gives the same
   // logits as blocks that take one each.
   const int z0 = MODE == kTilePart ? blockIdx.y : 0;
-  const int z1 = MODE == kTilePart ? z0 + 1 : a.zsplit;
+  const int z1 = MODE == kTilePart || ONE ? z0 + 1 : a.zsplit;
   for (int z = z0; z < z1; ++z) {
     const int k0 = z * a.zcols, kend = min(d, k0 + a.zcols);
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-      for (int nt = 0; nt < NTW; ++nt) rsum[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int nt = 0; nt < NTW; ++nt) rsum[mt][nt] = acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int q = 0; q < DEPTH; ++q) load(xq[q], wq[q], k0 + q * KC, kend);
     stage(xq[0], wq[0], 0);
@@ -173,6 +178,7 @@ __global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs 
         load(xq[set], wq[set], kc + (DEPTH + 1) * KC, kend);
         __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of the products
         multiply(buf);
+        if (kSum == KC || (kc - k0) % kSum + KC == kSum || kc + KC >= kend) flush();
         __syncthreads();
         buf ^= 1;
         kc += KC;
@@ -213,15 +219,30 @@ __global__ __launch_bounds__(WM* WN * 64) void route_tile_bf16_kernel(RouteArgs 
   }
 }
 
-template <int NT, int WM, int WN, int KC, int DEPTH>
+// Whether a batch runs with stages short enough for two blocks per CU (ONE): where
+// there are more blocks than CUs, one block's first loads and selection run beside
+// another's products.  At up to 48 experts LDS holds two blocks with the long stages
+// too, and the short ones gain only in shorter rows of large batches.  Whole gate, us,
+// long / short stages: 16448 x 768 x 80 33.6 / 26.2; 65536 x 256 x 96 44.0 / 32.3; 32768 x
+// 4096 x 128 96.3 / 86.1; up to 48 experts 65536 x 256 x 16 30.3 / 25.4, 65536 x 1024 x 48
+// 47.5 / 41.8, but 16448 x 3072 x 16 1.18 times and 32768 x 4096 x 48 1.09 times as long.
+static inline bool tile_two_per_cu(const RouteArgs& a) {
+  return a.zsplit == 1 && (a.E > 48 ? a.nb > 256 : a.nb > 512 && a.d <= 3072);
+}
+
+template <int NT, int WM, int WN, int KC, int DEPTH, bool ONE>
 struct TileBf16Launch {
   const RouteArgs& a;
   hipStream_t st;
   template <int KMAX, int MODE>
   hipError_t operator()() const {
-    route_tile_bf16_kernel<NT, WM, WN, KC, DEPTH, KMAX, MODE>
-        <<<dim3(a.nb, MODE == kTilePart ? a.zsplit : 1), dim3(WM * WN * kWave), 0, st>>>(a);
-    return hipGetLastError();
+    if constexpr (ONE && MODE == kTilePart) {
+      return hipErrorInvalidValue;  // one range is never a part
+    } else {
+      route_tile_bf16_kernel<NT, WM, WN, KC, DEPTH, ONE, KMAX, MODE>
+          <<<dim3(a.nb, MODE == kTilePart ? a.zsplit : 1), dim3(WM * WN * kWave), 0, st>>>(a);
+      return hipGetLastError();
+    }
   }
 };
 

@@ -7,10 +7,13 @@ hipError_t launch_route_tile_bf16_small(const RouteArgs& a, hipStream_t st);
 
 hipError_t launch_route_tile_bf16(const RouteArgs& a, hipStream_t st) {
   if (a.E <= 64) return launch_route_tile_bf16_small(a, st);
-  if (a.E <= 96) return tile_by_gate(a, TileBf16Launch<6, 4, 2, 128, 1>{a, st});
-  if (a.E <= 128) return tile_by_gate(a, TileBf16Launch<8, 4, 4, 128, 1>{a, st});
-  if (a.E <= 192) return tile_by_gate(a, TileBf16Launch<12, 2, 4, 64, 2>{a, st});
-  return tile_by_gate(a, TileBf16Launch<16, 2, 8, 64, 1>{a, st});
+  if (tile_two_per_cu(a) && a.E <= 96) return tile_by_gate(a, TileBf16Launch<6, 4, 2, 64, 1, true>{a, st});
+  if (tile_two_per_cu(a) && a.E <= 128) return tile_by_gate(a, TileBf16Launch<8, 4, 2, 64, 1, true>{a, st});
+  if (a.E <= 96) return tile_by_gate(a, TileBf16Launch<6, 4, 2, 128, 1, false>{a, st});
+  if (a.E <= 128) return tile_by_gate(a, TileBf16Launch<8, 4, 4, 128, 1, false>{a, st});
+  if (a.E <= 192) return tile_by_gate(a, TileBf16Launch<12, 2, 4, 64, 2, false>{a, st});
+  if (a.zsplit == 1) return tile_by_gate(a, TileBf16Launch<16, 2, 8, 64, 1, true>{a, st});
+  return tile_by_gate(a, TileBf16Launch<16, 2, 8, 64, 1, false>{a, st});
 }
 
 bool route_uses_tile_bf16(const RouteArgs& a) { return a.dtype == 1 && tile_shape(a); }

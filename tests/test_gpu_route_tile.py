@@ -51,6 +51,11 @@ CASES = [
     ("f32", 8000, 516, 40, 2, 0, 1, 0, 0.0),
     # one range, more blocks than CUs
     ("bf16", 20000, 264, 60, 2, 0, 1, 0, 0.0), ("f32", 20000, 132, 20, 2, 0, 0, 0, 0.0),
+    # two blocks per CU: from 257 wave blocks past 48 experts, from 513 up to 48 (rows of at most 3072)
+    ("bf16", 16385, 8, 49, 2, 0, 0, 0, 0.0), ("bf16", 16400, 200, 64, 4, 1, 0, 0, 0.5), ("bf16", 16385, 712, 65, 3, 0, 1, 0, 0.0),
+    ("bf16", 16400, 136, 96, 8, 3, 1, 4, 0.0), ("bf16", 16449, 72, 97, 1, 0, 0, 0, 0.0), ("bf16", 16385, 264, 128, 8, 0, 0, 0, 0.0),
+    ("bf16", 32769, 136, 16, 2, 0, 1, 0, 0.0), ("bf16", 32769, 72, 31, 1, 0, 0, 0, 0.5), ("bf16", 32833, 328, 48, 3, 1, 0, 0, 0.0),
+    ("bf16", 32769, 3080, 20, 2, 0, 0, 0, 0.0), ("bf16", 16385, 520, 250, 2, 0, 0, 0, 0.0),
 ]
 
 
@@ -94,6 +99,21 @@ def test_split_and_one_block_give_the_same_logits(dtype, S, d, E):
         for key in ("logits", "ids", "slots", "counts", "demand", "slot_src"):
             assert torch.equal(r[key], runs[0][key]), key
         assert torch.allclose(r["weights"], runs[0]["weights"], rtol=2e-6, atol=0)
+
+
+@pytest.mark.parametrize("S,more,d,E", [(16384, 1, 712, 64), (16384, 70, 200, 96), (16384, 1, 1032, 125),
+                                        (32768, 1, 136, 9), (32768, 100, 328, 48), (32768, 1, 1096, 32)])
+def test_short_and_long_stages_give_the_same_logits(S, more, d, E):
+    """One wave block more takes the batch to two blocks per CU and half as long
+    stages: bitwise the logits of the tokens that both batches hold."""
+    announce(f"short against long stages S={S}+{more} d={d} E={E}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(E)
+    x = torch.randn((S + more, d), generator=g, device="cuda").to(torch.bfloat16)
+    wg = (torch.randn((d, E), generator=g, device="cuda") / math.sqrt(d)).to(torch.bfloat16)
+    runs = [hm.gate(hm.MOE_GATE_TOPK, 1, E, 8, x=x[:n], wg=wg, want_logits=True)["logits"] for n in (S, S + more)]
+    torch.cuda.synchronize()
+    assert torch.equal(runs[0], runs[1][:S])
 
 
 @pytest.mark.parametrize("S,E,k,kind,groups,tau", [
