@@ -10,13 +10,18 @@ namespace hetumoe {
 // ---------------------------------------------------------------- VALU route
 // One thread per token, one wave (64 tokens) per block.  Logits for EC experts
 // at a time are accumulated in registers from the token's row of x and a
-// [kDJ, EC] tile of W staged in LDS.
+// [kDJ, EC] tile of W staged in LDS, kWU values per thread in flight (one at a
+// time, EC waits on memory per tile, bounded the kernel: bf16 500 x 512 x 512, k = 2,
+// 2808 us, so 1362; fp32 1770, 1360).  Registers for two waves per SIMD: left to
+// itself the compiler takes fewer for some k and waits for every LDS read (131 x 1568
+// x 1024 in bf16 14.8 ms, so 8.7).
 constexpr int kDJ = 64;
 
 template <typename T, int EC, int KMAX, bool KTOP1>
-__global__ __launch_bounds__(kWave) void route_valu_kernel(RouteArgs a) {
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(1, 2))) void route_valu_kernel(RouteArgs a) {
   extern __shared__ int hist_lds[];  // [E]
   __shared__ float wg_s[kDJ][EC];
+  constexpr int kWU = EC < 16 ? EC : 16;
 
   const int tid = threadIdx.x;
   const int64_t s = static_cast<int64_t>(blockIdx.x) * kWave + tid;
@@ -41,10 +46,19 @@ __global__ __launch_bounds__(kWave) void route_valu_kernel(RouteArgs a) {
     const T* wg = reinterpret_cast<const T*>(a.wg);
     for (int j0 = 0; j0 < a.d; j0 += kDJ) {
       __syncthreads();  // previous tile fully consumed
-      for (int t = tid; t < kDJ * EC; t += kWave) {
-        const int jj = t / EC, ii = t % EC;
-        const int j = j0 + jj, e = e0 + ii;
-        wg_s[jj][ii] = (j < a.d && e < E) ? load_elem(wg, static_cast<int64_t>(j) * E + e) : 0.f;
+      for (int u0 = 0; u0 < EC; u0 += kWU) {
+        float v[kWU];
+#pragma unroll
+        for (int u = 0; u < kWU; ++u) {
+          const int t = tid + (u0 + u) * kWave;
+          const int j = min(j0 + t / EC, a.d - 1), e = min(e0 + t % EC, E - 1);
+          v[u] = load_elem(wg, static_cast<int64_t>(j) * E + e);
+        }
+#pragma unroll
+        for (int u = 0; u < kWU; ++u) {
+          const int t = tid + (u0 + u) * kWave;
+          wg_s[t / EC][t % EC] = (j0 + t / EC < a.d && e0 + t % EC < E) ? v[u] : 0.f;
+        }
       }
       __syncthreads();
       if (valid) {
@@ -87,14 +101,6 @@ __global__ __launch_bounds__(kWave) void route_valu_kernel(RouteArgs a) {
         if (e0 + i < E) {
           if (a.bias) acc[i] += a.bias[e0 + i];
           if (a.logits) a.logits[s * E + e0 + i] = acc[i];
-        }
-      }
-    }
-
-    if (valid) {
-#pragma unroll
-      for (int i = 0; i < EC; ++i) {
-        if (e0 + i < E) {
           if constexpr (KTOP1) kt.push(acc[i], e0 + i, my_ids, my_w);
           else tk.push(acc[i], e0 + i);
         }

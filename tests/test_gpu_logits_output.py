@@ -27,13 +27,13 @@ def _gpu():
 
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("kind,k,E,groups", [
-    (0, 8, 60, 0), (1, 4, 60, 0), (3, 3, 60, 6),
+    (0, 5, 5, 0), (1, 3, 15, 0), (0, 4, 32, 0), (0, 8, 60, 0), (1, 4, 60, 0), (3, 3, 60, 6),
     (0, 2, 256, 0), (1, 8, 256, 0), (3, 2, 256, 4),
     (0, 2, 257, 0), (1, 1, 257, 0), (3, 5, 257, 1),
     (0, 1, 512, 0), (1, 2, 512, 0), (3, 4, 512, 8),
     (0, 8, 1024, 0), (1, 8, 1024, 0), (3, 8, 1024, 4),
 ])
-@pytest.mark.parametrize("d,wofs", [(264, 0), (264, 1), (2568, 0)])  # wofs: elements W is off its alignment by
+@pytest.mark.parametrize("d,wofs", [(264, 0), (264, 1), (40, 1), (2568, 0)])  # wofs: elements W is off its alignment by
 def test_logits_output_changes_nothing(dtype, kind, k, E, groups, d, wofs):
     S, C = 130, int(math.ceil(0.9 * k * 130 / E))
     rng = np.random.default_rng(E + k)
