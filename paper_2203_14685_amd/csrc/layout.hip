@@ -669,9 +669,15 @@ static void launch_token_rows_t(const RowArgs& a, hipStream_t st) {
   const int cpt = (a.k >= 3 && a.nch % (2 * kWave) == 0) ? 2 : 1;
   int rt = a.nch / cpt;  // threads a row would take
   // rows that are no whole waves take whole waves all the same where no fewer rows
-  // fit the block: the token of a wave is uniform then (scalar routing loads)
+  // fit the block: the token of a wave is uniform then (scalar routing loads).  Not
+  // for few rows, nor for one choice with several rows per block: dispatch to
+  // dispatch backward of 64 x 175 chunks, k = 1, 2, 4 11.5 / 11.2 / 11.7 us without
+  // whole waves, 12.2 / 11.6 / 12.1 with them; 4096 x 175, k = 4 64.4 / 61.8; 16384 x
+  // 175, k = 1 92.1 / 93.7; 4096 x 400, k = 1 59.2 / 56.4.
   const int whole = (rt + kWave - 1) / kWave * kWave;
-  if (rt < kRowThreads && kRowThreads / whole == kRowThreads / rt) rt = whole;
+  if (rt < kRowThreads && kRowThreads / whole == kRowThreads / rt && a.rows >= 1024 &&
+      (a.k > 1 || 2 * rt > kRowThreads))
+    rt = whole;
   const int tpr = rt <= kRowThreads ? rt : kRowThreads;
   const int rpb = rt <= kRowThreads ? kRowThreads / rt : 1;
   if (cpt == 2) launch_token_rows_w<T, WEIGHTED, true, 2>(a, tpr, rpb, st);

@@ -23,13 +23,15 @@ def _gpu():
 
 
 # chunks of 16 bytes per row: 1, 63, 65, 128, 129, 175, 257, 305, 384, 389, 511, 513, 705, 1025
-@pytest.mark.parametrize("nch", [1, 63, 65, 128, 129, 175, 257, 305, 384, 389, 511, 513, 705, 1025])
+@pytest.mark.parametrize("S,nch", [(77, n) for n in (1, 63, 65, 128, 129, 175, 257, 305, 384, 389, 511, 513, 705, 1025)] + [
+    # whole waves per token row from 1024 rows on (at k = 1 where a block holds one row)
+    (1023, 175), (1024, 103), (1024, 175), (1024, 257), (1030, 389)])
 @pytest.mark.parametrize("dtype,k", [("bf16", 2), ("f32", 3), ("bf16", 1)])
-def test_row_lengths(nch, dtype, k):
-    S, E = 77, 6
+def test_row_lengths(S, nch, dtype, k):
+    E = 6
     d = nch * (8 if dtype == "bf16" else 4)
-    C = 20 if k == 1 else 11 * k  # drops and empty slots
-    announce(f"layout rows nch={nch} {dtype} k={k}")
+    C = (20 if k == 1 else 11 * k) * S // 77  # drops and empty slots
+    announce(f"layout rows S={S} nch={nch} {dtype} k={k}")
     rng = np.random.default_rng(nch + k)
     L = rng.standard_normal((S, E)).astype(np.float32)
     L[:, 0] += 1.0
