@@ -156,6 +156,11 @@ MOE_API moe_status moe_gate_workspace_size(const moe_gate_params* p, size_t* byt
  *          logits; a workspace without that room (the histogram, 4 * k * E *
  *          ceil(S/64) bytes, plus 4 * S * E for the Dense-To-Sparse and
  *          hierarchical gates) is accepted and gives the same logits, slower.
+ * Rounding a token's logits may differ in their last bits between calls with
+ *          different S (how many ranges the sum over d is split into follows
+ *          from the batch) or another alignment of wg, and with them the
+ *          choice between two logits that are that near; otherwise they are the
+ *          same on every call.
  */
 MOE_API moe_status moe_gate(const moe_gate_params* p, const void* x, const void* wg,
                     const float* bias, const int32_t* token_ids, const float* noise,

@@ -1008,7 +1008,7 @@ __global__ __launch_bounds__(kBaseThreads) void base_tail_kernel(BaseArgs a, int
 
 // ---------------------------------------------------------------- outputs
 // ids, weights (sigmoid of the score) and the wave-block histogram [nb, E]
-// that the scan and assign kernels turn into slots
+// that the slot kernels (slots.hip) turn into slots.
 // With `status` (the asynchronous form) the outputs are written whatever the
 // outcome, every token with a valid expert (its current one, else s mod E, so
 // that the slot kernels that follow stay in bounds), and the outcome goes to

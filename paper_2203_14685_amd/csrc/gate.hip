@@ -18,7 +18,8 @@
 //             route_valu_kernel  more experts, or W not 16-byte aligned: one
 //                                thread per token;
 //             route_hash_kernel  the hash gate (no projection).
-//   scan, assign (slots.hip): the slots of the capacity rule.
+//   group_scan (large histograms only), assign: the slots of the capacity rule
+//           (slots.hip).
 #include <atomic>
 
 #include "select.hpp"

@@ -425,11 +425,6 @@ __device__ __forceinline__ void select_row(const float* lrow, int E, int k, int 
   }
 }
 
-// ---------------------------------------------------------------- wave-block histogram
-// hist[wb][r][e] = number of tokens of wave block wb whose rank-r choice is e.
-// Every wave of the block calls this (it synchronises the block); `active` waves
-// own a wave block, `s` is the calling lane's token.  The ids are read back from
-// global memory, where the same thread wrote them.
 // Hierarchical top-k (Sec. 3.1, H Topk) on a compile-time slice: the best expert
 // over all E (with the full softmax sum), its group of Gs contiguous experts,
 // then the k best experts of that group.  Weights: softmax over the k chosen
@@ -470,6 +465,11 @@ __device__ __forceinline__ void select_token_htopk_c(const float* lrow, int k, i
   }
 }
 
+// ---------------------------------------------------------------- wave-block histogram
+// hist[wb][r][e] = number of tokens of wave block wb whose rank-r choice is e.
+// Every wave of the block calls this (it synchronises the block); `active` waves
+// own a wave block, `s` is the calling lane's token.  The ids are read back from
+// global memory, where the same thread wrote them.
 __device__ __forceinline__ void wave_block_hist(int* lds_w, bool active, int64_t s, bool valid, int wb,
                                                 const RouteArgs& a) {
   const int lane = lane_id();

@@ -82,10 +82,9 @@ def test_dense_ties_logits_in(E, k, kind, normalize):
 
 
 @pytest.mark.parametrize("S,E,k,kind,normalize", [
-    # histograms (k E rows of one count per 64-token wave block) past the
-    # one-launch scan-and-assign limit, so that the scan and the assignment run
-    # as two kernels: ragged wave-block counts (313, 516, 625), kTop1, top-8
-    # and E = 1024
+    # histograms (a row of k E counts per 64-token wave block) past the 32768 counts
+    # that one launch takes, so that running sums of groups of rows come first:
+    # ragged wave-block counts (313, 516, 625), kTop1, top-8 and E = 1024
     (20000, 64, 2, 0, 1), (33000, 64, 1, 0, 0), (32768, 64, 4, 1, 0), (40000, 16, 8, 0, 1),
     (9000, 1024, 2, 0, 0),
 ])
@@ -153,9 +152,9 @@ def test_projection_odd_shapes(dtype, d, E, k):
     ("bf16", 8, 2, 0, 1, 1032, True, 700), ("f32", 32, 3, 0, 0, 516, False, 1),
 ])
 def test_split_projection_shapes(dtype, E, k, kind, normalize, d, bias, S):
-    """Projections on the vector ALUs with 8 lanes per token (E in 8..64, d a
-    whole number of 16-byte chunks): W staged in several phases with a ragged
-    last one, ragged token tails, kTop1 groups down to one expert."""
+    """Tiled projections (E in 8..64, d a whole number of 16-byte chunks): several
+    stages of W with a ragged last one, K split over blocks, ragged token tails,
+    kTop1 groups down to one expert."""
     announce(f"split projection dtype={dtype} E={E} k={k} kind={kind} d={d} bias={bias} S={S}")
     w = dict(kind=kind, k=k, normalize=normalize, dtype=dtype, S=S, d=d, E=E, cf=1.0)
     if bias:
@@ -168,22 +167,22 @@ def test_split_projection_shapes(dtype, E, k, kind, normalize, d, bias, S):
 
 
 @pytest.mark.parametrize("E,k,kind,normalize,d,bias,S", [
-    # W staged through LDS (4 lanes per token select)
+    # tiled: W staged in LDS per K stage
     (16, 1, 1, 0, 256, False, 300), (48, 1, 0, 0, 256, False, 300), (64, 4, 1, 0, 768, True, 300),
     (80, 3, 0, 1, 256, False, 300), (96, 8, 0, 0, 128, True, 300), (112, 2, 0, 0, 384, False, 300),
     (128, 8, 1, 0, 256, True, 300), (128, 2, 0, 1, 384, False, 300), (48, 3, 1, 0, 256, False, 300),
     (64, 8, 1, 0, 256, True, 300), (128, 4, 1, 0, 384, False, 300), (80, 5, 1, 0, 256, False, 300),
-    # W held in registers: eight waves up to d * E = 64 K (8 lanes per token select)
+    # W held in registers by eight waves (8 lanes per token select)
     (32, 2, 0, 1, 512, True, 300), (64, 4, 1, 0, 1024, True, 300), (128, 8, 0, 1, 512, False, 300),
     (16, 2, 0, 0, 2048, False, 300), (32, 8, 1, 0, 1024, True, 300), (64, 1, 0, 0, 512, False, 300),
     (64, 2, 0, 1, 512, True, 20000),
-    # ... four waves up to 128 K (4 lanes per token select); S = 20000 and 40000
-    # give blocks two and three wave blocks
+    # ... d * E = 64 K and 128 K; S = 20000 and 40000 give blocks two and three
+    # wave blocks
     (32, 2, 0, 1, 2048, True, 20000), (32, 8, 1, 0, 2048, False, 300), (64, 8, 0, 1, 2048, True, 300),
     (64, 4, 1, 0, 2048, False, 40000), (64, 1, 0, 0, 2048, True, 77), (128, 3, 0, 0, 1024, True, 700),
     (128, 8, 1, 0, 1024, False, 20000),
-    # W^T staged per K phase (persistent, one block per CU); S = 40000 gives some
-    # blocks three wave blocks, one of them without a partner
+    # tiled, longer rows (128 x 1024: W held in registers); S = 40000: two blocks per
+    # CU
     (64, 2, 0, 1, 1536, True, 40000), (128, 1, 1, 0, 1024, False, 3000), (16, 4, 0, 1, 4096, True, 300),
     (64, 4, 1, 0, 3072, True, 300), (32, 8, 0, 1, 4096, False, 700),
 ])
