@@ -221,13 +221,14 @@ void route_tile_bf16_kernel(RouteArgs a) {
 
 // Whether a batch runs with stages short enough for two blocks per CU (ONE): where
 // there are more blocks than CUs, one block's first loads and selection run beside
-// another's products.  At up to 48 experts LDS holds two blocks with the long stages
-// too, and the short ones gain only in shorter rows of large batches.  Whole gate, us,
-// long / short stages: 16448 x 768 x 80 33.6 / 26.2; 65536 x 256 x 96 44.0 / 32.3; 32768 x
-// 4096 x 128 96.3 / 86.1; up to 48 experts 65536 x 256 x 16 30.3 / 25.4, 65536 x 1024 x 48
-// 47.5 / 41.8, but 16448 x 3072 x 16 1.18 times and 32768 x 4096 x 48 1.09 times as long.
+// another's products.  Up to 48 experts LDS holds two blocks with the long stages
+// too, and the short ones gain only past 512 blocks.  Whole gate, us, long / short
+// stages: 16448 x 768 x 80 33.6 / 26.2; 65536 x 256 x 96 44.0 / 32.3; 32768 x 4096 x 128
+// 96.3 / 86.1; up to 48 experts 65536 x 256 x 16 30.3 / 25.4, 65536 x 8192 x 16 250 / 220,
+// 33000 x 4096 x 48 78 / 63, 131072 x 3080 x 48 200 / 205, and in 512 blocks 32768 x 4096 x
+// 48 1.09 times as long.
 static inline bool tile_two_per_cu(const RouteArgs& a) {
-  return a.zsplit == 1 && (a.E > 48 ? a.nb > 256 : a.nb > 512 && a.d <= 3072);
+  return a.zsplit == 1 && a.nb > (a.E > 48 ? 256 : 512);
 }
 
 template <int NT, int WM, int WN, int KC, int DEPTH, bool ONE>

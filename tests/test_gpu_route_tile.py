@@ -51,7 +51,7 @@ CASES = [
     ("f32", 8000, 516, 40, 2, 0, 1, 0, 0.0),
     # one range, more blocks than CUs
     ("bf16", 20000, 264, 60, 2, 0, 1, 0, 0.0), ("f32", 20000, 132, 20, 2, 0, 0, 0, 0.0),
-    # two blocks per CU: from 257 wave blocks past 48 experts, from 513 up to 48 (rows of at most 3072)
+    # two blocks per CU: from 257 wave blocks past 48 experts, from 513 up to 48
     ("bf16", 16385, 8, 49, 2, 0, 0, 0, 0.0), ("bf16", 16400, 200, 64, 4, 1, 0, 0, 0.5), ("bf16", 16385, 712, 65, 3, 0, 1, 0, 0.0),
     ("bf16", 16400, 136, 96, 8, 3, 1, 4, 0.0), ("bf16", 16449, 72, 97, 1, 0, 0, 0, 0.0), ("bf16", 16385, 264, 128, 8, 0, 0, 0, 0.0),
     ("bf16", 32769, 136, 16, 2, 0, 1, 0, 0.0), ("bf16", 32769, 72, 31, 1, 0, 0, 0, 0.5), ("bf16", 32833, 328, 48, 3, 1, 0, 0, 0.0),
