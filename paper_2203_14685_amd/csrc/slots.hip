@@ -213,6 +213,10 @@ hipError_t launch_assign(const AssignArgs& a, hipStream_t st) {
   // a few counts only: small blocks start sooner
   if (Q <= 256 && a.k <= 4 && Q * a.nb <= 4096) launch_assign_t<256, 1>(a, F, st);
   else if (WB == 1) launch_assign_t<1024, 1>(a, F, st);
+  // few sums to add after group_scan: half the threads start and meet sooner (512 /
+  // 1024: hash gate, 65536 tokens, E = 64 10.2 / 10.8; given logits 100000 x 24, k = 2
+  // 15.4 / 16.7); the counts themselves need them all (32768 x 64, k = 1 12.9 / 11.2)
+  else if (WB == 4 && F > 1 && Q <= 64 && a.k <= 4) launch_assign_t<512, 4>(a, F, st);
   else if (WB == 4) launch_assign_t<1024, 4>(a, F, st);
   else launch_assign_t<1024, 16>(a, F, st);
   return hipGetLastError();

@@ -43,6 +43,7 @@ def reference(ids, E, C):
     (32705, 60, 1), (32833, 64, 1), (33000, 16, 8), (33001, 512, 8),       # four wave blocks per block, ragged
     (128001, 128, 8),                                                      # groups of 64 rows
     (65536, 5, 1), (65600, 5, 1), (65601, 300, 1), (131072, 3, 2), (131073, 3, 2),  # sixteen wave blocks per block
+    (50000, 24, 2), (66001, 16, 4), (66001, 13, 5), (33100, 64, 1),                 # 512 threads after group_scan, and not
     (131200, 64, 8), (131200, 65, 8),                                      # 512 columns, and too many for sixteen
     (200, 2, 1), (4000, 1, 1), (2100, 3, 3),                               # many partial sums per column
 ])
